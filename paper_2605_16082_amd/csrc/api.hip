@@ -54,13 +54,36 @@ struct Plan {
   // cells deepest first (stable): the dispatch order of the column solves
   std::vector<int32_t> cell_order;
   int n_tiles[kTileChoices] = {};
+  // blocks of the layer-parallel column solves (empty: a column deeper than
+  // kColSolveMaxLayers, the serial sweeps are used)
+  std::vector<ColTile> col_tiles;
+  int col_max_np = 0;
   // workspace offsets (bytes)
   size_t o_cell_base, o_cell_lbase, o_nlay, o_nbr_slot, o_nbr_meta, o_nbr_col, o_col_member, o_member_off,
       o_geo, o_geo32, o_xy, o_zl, o_zl32, o_tiles[kTileChoices], o_tiles_bucket, o_stage_a, o_stage_b, o_scratch,
       o_tfac,
-      o_colmass, o_msum, o_flag, o_kpart, o_kh, o_hface, o_hoff, o_hslot, o_hdepth, o_hidx, o_corder, total;
+      o_colmass, o_msum, o_flag, o_kpart, o_kh, o_hface, o_hoff, o_hslot, o_hdepth, o_hidx, o_corder,
+      o_ctiles, total;
   size_t state_bytes, velocity_bytes;
 };
+
+// Column groups of the layer-parallel solves: per cell the largest power of two
+// of columns whose prisms fit a block of kColSolveMaxPrisms threads (4 columns at 64
+// layers, where a lane's 16-byte copies still hold whole columns; blocks of 512 with
+// twice the columns were 10-15% slower).  Deepest cells first, as the longest.
+void plan_column_blocks(Plan& P) {
+  P.col_tiles.clear();
+  P.col_max_np = 0;
+  if (P.max_layers > kColSolveMaxLayers) return;
+  for (int32_t k : P.cell_order) {
+    const int D = P.cell_depth[k];
+    int g = 6;
+    while ((D << g) > kColSolveMaxPrisms) --g;
+    for (int c0 = 0; c0 < kCell && k * kCell + c0 < P.C; c0 += 1 << g)
+      P.col_tiles.push_back({P.cell_base[k] + c0, P.cell_lbase[k] + c0, k * kCell + c0, (uint16_t)D, (uint16_t)g});
+    P.col_max_np = std::max(P.col_max_np, D << g);
+  }
+}
 
 sdg_status plan_mesh(const sdg_mesh_desc* d, Plan& P) {
   if (!d) return fail(SDG_E_ARG, "mesh description is NULL");
@@ -176,6 +199,7 @@ sdg_status plan_mesh(const sdg_mesh_desc* d, Plan& P) {
   for (int k = 0; k < P.n_cells; ++k) P.cell_order[k] = k;
   std::stable_sort(P.cell_order.begin(), P.cell_order.end(),
                    [&](int32_t x, int32_t y) { return P.cell_depth[x] > P.cell_depth[y]; });
+  plan_column_blocks(P);
   P.halo_max = 0;
   for (int k = 0; k < P.n_cells; ++k) {
     P.halo_max = std::max(P.halo_max, P.halo_off[k + 1]);
@@ -226,6 +250,7 @@ sdg_status plan_mesh(const sdg_mesh_desc* d, Plan& P) {
   P.o_hdepth = take(sizeof(int32_t) * std::max<size_t>(P.halo_off[P.n_cells], 1));
   P.o_hidx = take(sizeof(int32_t) * 3 * (size_t)P.CS);
   P.o_corder = take(sizeof(int32_t) * (size_t)P.n_cells);
+  P.o_ctiles = take(sizeof(ColTile) * std::max<size_t>(P.col_tiles.size(), 1));
   P.total = o;
   return SDG_OK;
 }
@@ -537,6 +562,7 @@ sdg_status sdg_mesh_upload(sdg_ctx* ctx, const sdg_mesh_desc* mesh, void* dev_wo
       {P.o_hdepth, hdepth.data(), sizeof(int32_t) * hdepth.size()},
       {P.o_hidx, hidx.data(), sizeof(int32_t) * hidx.size()},
       {P.o_corder, P.cell_order.data(), sizeof(int32_t) * P.cell_order.size()},
+      {P.o_ctiles, P.col_tiles.data(), sizeof(ColTile) * P.col_tiles.size()},
   };
   static_assert(kTileChoices == 7, "one copy per tile table");
   for (const Cp& cp : cps) {
@@ -742,6 +768,7 @@ sdg_status enqueue_stage(sdg_ctx* ctx, int stage, const void* Tn, const void* Ts
 SolveArgs solve_args(sdg_ctx* ctx, const void* Tstar, void* Tout, double dt) {
   SolveArgs a{};
   a.m = ctx->dm;
+  a.keep_p = !ctx->plan.col_tiles.empty();
   a.n_fields = ctx->plan.F;
   a.Tstar = Tstar;
   a.Tout = Tout;
@@ -752,9 +779,8 @@ SolveArgs solve_args(sdg_ctx* ctx, const void* Tstar, void* Tout, double dt) {
   return a;
 }
 
-// The block-Thomas factors for a solve over dt: kept in the solve scratch
-// until kappa, the parameters or the mesh change, or the adjoint's
-// transposed solve reuses the scratch.
+// The column factors for a solve over dt: kept in the solve scratch until
+// kappa, the parameters or the mesh change.
 sdg_status ensure_factors(sdg_ctx* ctx, double dt, hipStream_t strm) {
   if (ctx->efac_valid && ctx->efac_dt == dt) return SDG_OK;
   hipError_t e = launch_vsolve(solve_args(ctx, nullptr, nullptr, dt), ctx->plan.fp32, ctx->plan.prec == SDG_FP32,
@@ -765,9 +791,28 @@ sdg_status ensure_factors(sdg_ctx* ctx, double dt, hipStream_t strm) {
   return SDG_OK;
 }
 
+hipError_t enqueue_column_solve(sdg_ctx* ctx, const void* Tstar, void* Tout, double dt, bool transposed,
+                                hipStream_t strm) {
+  ColSolveArgs a{};
+  a.m = ctx->dm;
+  a.tiles = reinterpret_cast<const ColTile*>(ctx->ws + ctx->plan.o_ctiles);
+  a.n_tiles = (int)ctx->plan.col_tiles.size();
+  a.max_np = ctx->plan.col_max_np;
+  a.n_fields = ctx->plan.F;
+  a.aligned = (reinterpret_cast<uintptr_t>(Tstar) & 15) == 0;
+  a.Tstar = Tstar;
+  a.Tout = Tout;
+  a.kappa = ctx->kappa;
+  a.fac = ctx->scratch;
+  a.dt = dt;
+  a.eta = ctx->eta;
+  return launch_column_solve(a, ctx->plan.fp32, ctx->plan.prec == SDG_FP32, transposed, strm);
+}
+
 // The transposed system's factors for the adjoint's solve over dt, kept in
 // their own array (the forward factors stay valid).
 sdg_status ensure_tfactors(sdg_ctx* ctx, double dt, hipStream_t strm) {
+  if (!ctx->plan.col_tiles.empty()) return ensure_factors(ctx, dt, strm);   // both systems share the pivots
   if (ctx->tfac_valid && ctx->tfac_dt == dt) return SDG_OK;
   hipError_t e = launch_tsolve(ctx->dm, ctx->plan.F, nullptr, nullptr, ctx->kappa, ctx->tfac, dt, ctx->eta, true, strm);
   if (e != hipSuccess) return hip_fail(e, "transposed column factor launch");
@@ -776,14 +821,22 @@ sdg_status ensure_tfactors(sdg_ctx* ctx, double dt, hipStream_t strm) {
   return SDG_OK;
 }
 
+// mu from Z: the adjoint's solve over dt, with the factors in place.
+hipError_t enqueue_tsolve(sdg_ctx* ctx, const double* Z, double* mu, double dt, hipStream_t strm) {
+  if (!ctx->plan.col_tiles.empty()) return enqueue_column_solve(ctx, Z, mu, dt, true, strm);
+  return launch_tsolve(ctx->dm, ctx->plan.F, Z, mu, ctx->kappa, ctx->tfac, dt, ctx->eta, false, strm);
+}
+
 // the solve's dt in a step of the context's scheme
 double step_solve_dt(const sdg_ctx* ctx) { return ctx->scheme == SDG_SCHEME_SPLIT_IMEX ? 0.5 * ctx->dt : ctx->dt; }
 
 sdg_status enqueue_solve(sdg_ctx* ctx, const void* Tstar, void* Tout, double dt, hipStream_t strm) {
   sdg_status st = ensure_factors(ctx, dt, strm);
   if (st != SDG_OK) return st;
-  hipError_t e = launch_vsolve(solve_args(ctx, Tstar, Tout, dt), ctx->plan.fp32, ctx->plan.prec == SDG_FP32,
-                               false, strm);
+  hipError_t e = !ctx->plan.col_tiles.empty()
+                     ? enqueue_column_solve(ctx, Tstar, Tout, dt, false, strm)
+                     : launch_vsolve(solve_args(ctx, Tstar, Tout, dt), ctx->plan.fp32, ctx->plan.prec == SDG_FP32,
+                                     false, strm);
   if (e != hipSuccess) return hip_fail(e, "vertical solve launch");
   return SDG_OK;
 }
@@ -1267,8 +1320,7 @@ sdg_status sdg_step_adjoint(sdg_ctx* ctx, const void* dev_z_next, void* dev_z_ou
   hipStream_t s = ctx->stream;
   sdg_status fst = ensure_tfactors(ctx, ctx->dt, s);
   if (fst != SDG_OK) return fst;
-  hipError_t e = launch_tsolve(ctx->dm, P.F, static_cast<const double*>(dev_z_next), mu, ctx->kappa,
-                               ctx->tfac, ctx->dt, ctx->eta, false, s);
+  hipError_t e = enqueue_tsolve(ctx, static_cast<const double*>(dev_z_next), mu, ctx->dt, s);
   if (e != hipSuccess) return hip_fail(e, "transposed solve launch");
   if (dev_dkappa) {
     e = launch_kappa_gradient(ctx->dm, ctx->tiles[1], P.n_tiles[1], P.F, mu, static_cast<const double*>(dev_x_next),
@@ -1350,7 +1402,7 @@ sdg_status adjoint_imex(sdg_ctx* ctx, const char* who, const void* dev_z_next, v
   if (e == hipSuccess) {
     sdg_status fst = ensure_tfactors(ctx, h, s);
     if (fst != SDG_OK) return fst;
-    e = launch_tsolve(ctx->dm, P.F, w, mu, ctx->kappa, ctx->tfac, h, ctx->eta, false, s);
+    e = enqueue_tsolve(ctx, w, mu, h, s);
   }
   if (e == hipSuccess && dev_dkappa)
     e = launch_kappa_gradient(ctx->dm, ctx->tiles[1], P.n_tiles[1], P.F, mu, xh, ctx->kpart, ctx->eta, h,

@@ -106,8 +106,36 @@ struct StageArgs {
   double a, b;         // Tout = a Tn + b (Ts + dt L)
 };
 
+// Layer-parallel column solves: a block takes 2^log2cols consecutive columns of a
+// cell over the cell's depth, one thread per prism.
+struct ColTile {
+  int32_t base;       // prism slot of the first column's layer 0
+  int32_t lbase;      // its level slot
+  int32_t col;        // its column slot
+  uint16_t depth;     // layers of the cell
+  uint16_t log2cols;
+};
+constexpr int kColSolveMaxLayers = 64;    // deeper meshes take the serial sweeps
+constexpr int kColSolveMaxPrisms = 256;   // prisms (threads) of a block
+static_assert(kColSolveMaxPrisms / kColSolveMaxLayers >= 4, "16-byte copies need 4 columns a block");
+
+struct ColSolveArgs {
+  DevMesh m;
+  const ColTile* tiles;
+  int32_t n_tiles;
+  int32_t max_np;        // largest depth << log2cols of the table
+  int32_t n_fields;
+  int32_t aligned;       // Tstar is 16-byte aligned (its rows then are)
+  const void* Tstar;     // may be the same array as Tout
+  void* Tout;
+  const double* kappa;
+  const void* fac;       // the kept P_l, row-major: [5 pairs][n_slots] of the solve's arithmetic type
+  double dt, eta;
+};
+
 struct SolveArgs {
   DevMesh m;
+  int32_t keep_p;        // factor sweep: keep P_l for the layer-parallel solve instead of E_l
   int32_t n_fields;
   const void* Tstar;
   void* Tout;
@@ -144,9 +172,13 @@ hipError_t launch_geometry(const DevMesh& m, double* geo, float* geo32, hipStrea
 hipError_t launch_z32(const DevMesh& m, float* zl32, hipStream_t s);
 hipError_t launch_stage(const StageArgs& a, bool fp32, bool w_zero, bool rhs_only,
                         bool read_tn, hipStream_t s);
-// factor = true: compute and keep the block-Thomas factors E_l for (kappa, dt,
-// eta) in a.scratch (the fields are not read); false: solve with kept factors.
+// factor = true: compute and keep the factors for (kappa, dt, eta) in a.scratch
+// (the fields are not read): E_l, or with a.keep_p the P_l of the layer-parallel
+// solve; false: serial solve with kept E_l.
 hipError_t launch_vsolve(const SolveArgs& a, bool fp32_state, bool fp32_solve, bool factor, hipStream_t s);
+// The layer-parallel solve (transposed: the adjoint's, FP64 only) with kept P_l.
+hipError_t launch_column_solve(const ColSolveArgs& a, bool fp32_state, bool fp32_solve, bool transposed,
+                               hipStream_t s);
 // Matrix-free D_vu (down = true) / D_vd column solves; fp32_arith only with fp32_state.
 hipError_t launch_column_dv(const DevMesh& m, bool down, int n_comp, const void* F, void* X, bool fp32_state,
                             bool fp32_arith, hipStream_t s);
