@@ -137,110 +137,118 @@ __device__ __forceinline__ ColGeo<R> load_colgeo(const DevMesh& m, uint32_t co) 
 }
 
 // ===========================================================================
-// Per-prism factors (field independent), then one field at a time.
-//
-// Everything that depends only on geometry and velocity is computed once per
-// prism: the volume flux factors at the 12 volume points, the upwind weights
-// of the lateral and horizontal faces, and the cofactors of Mz.  Each field
-// then needs only its own nodal values and its neighbours' traces, so the
-// values live at any time are the factors plus one field's working set.
+// Term by term, all fields: a prism's residuals res[NF][6] are carried through
+// the volume term, the lateral faces 0, 1, 2, the top and the bottom face, in
+// this order.  Of the field-independent factors only one term's are live at a
+// time, and each term's end is a point that the compiler may not reorder over
+// (formed); the one-thread-per-prism kernel requests a term's neighbour values
+// one term ahead.  What bounds the kernels is the latency of their loads at the
+// one to three wavefronts per SIMD that their registers allow.  Before, all
+// factors were formed first, the fields went one at a time, and the compiler
+// placed the loads; registers of the third stage before and after: FP64 2 fields
+// 304 -> 237 (one thread per prism: two wavefronts for one), FP32 2 fields
+// 184 -> 142 (three for two), FP64 column walk of 4 fields 462 -> 413.  Third
+// stage of sigma-grid boxes, 64 columns a cell, before and after:
+//   one thread per prism  FP64 4 fields, 6.0 M prisms   1.87 -> 1.49 ms
+//                         FP64 3 fields with w, 0.35 M  82   -> 66 us
+//                         FP32 2 fields, 0.71 M         56   -> 47 us
+//                         FP64 1 field, 1.0 M           100  -> 97 us
+//   column walk, 12       FP64 4 fields, 6.0 M prisms   1.20 -> 1.14 ms
+//                         FP64 4 fields, 2.6 M          546  -> 506 us
+//                         FP32 4 fields, 6.0 M          0.64 -> 0.64 ms
+// own(f, i) gives the prism's nodal value i of field f.
 // ===========================================================================
 
 // No instruction moves across this point.
 __device__ __forceinline__ void phase() { __builtin_amdgcn_sched_barrier(0); }
 
-// Volume term factors: with alpha = y_eta u - x_eta v, beta = x_xi v - y_xi u
-// at volume point (k, q):
-//   Vx = w_q z_zeta alpha, Ve = w_q z_zeta beta,
-//   Vz = w_q (J_h w - z_xi alpha - z_eta beta).
-// The field's value at the point is sum_a lambda_a(q) ta_k[a] (ta_k: the
-// field at the three nodes interpolated to zeta_k), so the sums over q of
-// the same quadrature are contracted once per prism into the field-free
-//   Px_k[a] = sum_q lambda_a(q) Vx,  Pe_k[a] = sum_q lambda_a(q) Ve,
-//   G_k[n][a] = sum_q lambda_n(q) lambda_a(q) Vz   (symmetric),
-// and each field only takes ta_k . Px_k, ta_k . Pe_k and G_k ta_k
-// (42 multiply-adds a field instead of 108, and 24 values kept instead of 36).
-template <typename R>
-struct VolF {
-  R Px[2][3], Pe[2][3], G[2][6];   // G: symmetric 3x3, entries 00 11 22 01 02 12
-};
-
-template <typename R, bool WZ>
-__device__ __forceinline__ void volume_factors(const ColGeo<R>& g, const R zt[3], const R zb[3], const R dz[3],
-                                               const R u[6], const R v[6], const R w[6], VolF<R>& F) {
-  const R xxi = g.xxi, xet = g.xet, yxi = g.yxi, yet = g.yet, Jh = g.Jh;
+// The residuals are formed up to here: without it the compiler sinks the whole
+// arithmetic of a prism into the branch around its stores, behind all of its
+// loads, whose values then all wait in registers.
+template <typename R, int NF>
+__device__ __forceinline__ void formed(R (&res)[NF][6]) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const R tk = R(kZt[k]), bk = R(kZb[k]);
-    R ua[3], va[3], wa[3];
+  for (int f = 0; f < NF; ++f)
 #pragma unroll
-    for (int n = 0; n < 3; ++n) {
-      ua[n] = tk * u[n] + bk * u[n + 3];
-      va[n] = tk * v[n] + bk * v[n + 3];
-      wa[n] = WZ ? R(0) : tk * w[n] + bk * w[n + 3];
-    }
-    const R z_xi = tk * (zt[1] - zt[0]) + bk * (zb[1] - zb[0]);
-    const R z_et = tk * (zt[2] - zt[0]) + bk * (zb[2] - zb[0]);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) F.Px[k][i] = F.Pe[k][i] = R(0);
-#pragma unroll
-    for (int i = 0; i < 6; ++i) F.G[k][i] = R(0);
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      const R l0 = R(kL0[q]), l1 = R(kL1[q]), l2 = R(kL2[q]), wq = R(kTw[q]);
-      const R uq = l0 * ua[0] + l1 * ua[1] + l2 * ua[2];
-      const R vq = l0 * va[0] + l1 * va[1] + l2 * va[2];
-      const R zz = R(0.5) * (l0 * dz[0] + l1 * dz[1] + l2 * dz[2]);
-      const R al = yet * uq - xet * vq;
-      const R be = xxi * vq - yxi * uq;
-      const R vx = wq * zz * al;
-      const R ve = wq * zz * be;
-      R vz = -(z_xi * al + z_et * be);
-      if (!WZ) vz += Jh * (l0 * wa[0] + l1 * wa[1] + l2 * wa[2]);
-      vz *= wq;
-      F.Px[k][0] += l0 * vx;
-      F.Px[k][1] += l1 * vx;
-      F.Px[k][2] += l2 * vx;
-      F.Pe[k][0] += l0 * ve;
-      F.Pe[k][1] += l1 * ve;
-      F.Pe[k][2] += l2 * ve;
-      F.G[k][0] += R(kL0[q] * kL0[q]) * vz;
-      F.G[k][1] += R(kL1[q] * kL1[q]) * vz;
-      F.G[k][2] += R(kL2[q] * kL2[q]) * vz;
-      F.G[k][3] += R(kL0[q] * kL1[q]) * vz;
-      F.G[k][4] += R(kL0[q] * kL2[q]) * vz;
-      F.G[k][5] += R(kL1[q] * kL2[q]) * vz;
-    }
-  }
+    for (int i = 0; i < 6; ++i) asm volatile("" : "+v"(res[f][i]));
+  phase();
 }
 
-// res[i] = int_K T U.grad(phi_i) dV for one field.
-template <typename R>
-__device__ __forceinline__ void volume_field(const VolF<R>& F, const R T[6], R res[6]) {
-  R sx[2], se[2], sz[3] = {R(0), R(0), R(0)};
+// Volume term: with alpha = y_eta u - x_eta v, beta = x_xi v - y_xi u at
+// volume point (k, q), each field takes, with ta_k its three nodal values
+// interpolated to zeta_k, ta_k . Px_k, ta_k . Pe_k and G_k ta_k, where
+//   Px_k[a] = sum_q w_q lambda_a z_zeta alpha,  Pe_k[a] = sum_q w_q lambda_a z_zeta beta,
+//   G_k[n][a] = sum_q w_q lambda_n lambda_a (J_h w - z_xi alpha - z_eta beta).
+// z_zeta, alpha, beta and the bracket are linear over the triangle and the
+// degree-4 rule is exact on the cubics, so with nodal values x_b, y_c
+//   sum_q w_q lambda_a x y = (X Y + x_a Y + X y_a + x.y + 2 x_a y_a) / 120
+// (X, Y the sums over the nodes), and the same with x = lambda_n: about 150
+// multiply-adds for both k where the sums over the points take 400.
+template <typename R, int NF, bool WZ, typename Own>
+__device__ __forceinline__ void volume_term(const ColGeo<R>& g, const R zt[3], const R zb[3], const R dz[3],
+                                            const R u[6], const R v[6], const R w[6], Own own, R (&res)[NF][6]) {
+  const R xxi = g.xxi, xet = g.xet, yxi = g.yxi, yet = g.yet, Jh = g.Jh;
+  R Px[2][3], Pe[2][3], G[2][6];   // G: symmetric 3x3, entries 00 11 22 01 02 12
+  const R zs = dz[0] + dz[1] + dz[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const R tk = R(kZt[k]), bk = R(kZb[k]);
-    R ta[3];
+    const R z_xi = tk * (zt[1] - zt[0]) + bk * (zb[1] - zb[0]);
+    const R z_et = tk * (zt[2] - zt[0]) + bk * (zb[2] - zb[0]);
+    R al[3], be[3], c[3];
 #pragma unroll
-    for (int n = 0; n < 3; ++n) ta[n] = tk * T[n] + bk * T[n + 3];
-    sx[k] = ta[0] * F.Px[k][0] + ta[1] * F.Px[k][1] + ta[2] * F.Px[k][2];
-    se[k] = ta[0] * F.Pe[k][0] + ta[1] * F.Pe[k][1] + ta[2] * F.Pe[k][2];
-    sz[0] += F.G[k][0] * ta[0] + F.G[k][3] * ta[1] + F.G[k][4] * ta[2];
-    sz[1] += F.G[k][3] * ta[0] + F.G[k][1] * ta[1] + F.G[k][5] * ta[2];
-    sz[2] += F.G[k][4] * ta[0] + F.G[k][5] * ta[1] + F.G[k][2] * ta[2];
+    for (int n = 0; n < 3; ++n) {
+      const R ua = tk * u[n] + bk * u[n + 3];
+      const R va = tk * v[n] + bk * v[n + 3];
+      al[n] = yet * ua - xet * va;
+      be[n] = xxi * va - yxi * ua;
+      R x = -(z_xi * al[n] + z_et * be[n]);
+      if (!WZ) x += Jh * (tk * w[n] + bk * w[n + 3]);
+      c[n] = R(1.0 / 120.0) * x;
+    }
+    const R as = al[0] + al[1] + al[2], bs = be[0] + be[1] + be[2], cs = c[0] + c[1] + c[2];
+    const R ax = zs * as + (dz[0] * al[0] + dz[1] * al[1] + dz[2] * al[2]);
+    const R bx = zs * bs + (dz[0] * be[0] + dz[1] * be[1] + dz[2] * be[2]);
+#pragma unroll
+    for (int n = 0; n < 3; ++n) {
+      Px[k][n] = R(1.0 / 240.0) * (ax + zs * al[n] + dz[n] * (as + R(2) * al[n]));
+      Pe[k][n] = R(1.0 / 240.0) * (bx + zs * be[n] + dz[n] * (bs + R(2) * be[n]));
+      G[k][n] = R(2) * cs + R(4) * c[n];
+    }
+    G[k][3] = cs + c[0] + c[1];
+    G[k][4] = cs + c[0] + c[2];
+    G[k][5] = cs + c[1] + c[2];
   }
-  // dphi/dxi = dlambda/dxi * (t or b), dphi/dzeta = +-lambda/2
-  const R sxt = R(kZt[0]) * sx[0] + R(kZt[1]) * sx[1];
-  const R sxb = R(kZb[0]) * sx[0] + R(kZb[1]) * sx[1];
-  const R set = R(kZt[0]) * se[0] + R(kZt[1]) * se[1];
-  const R seb = R(kZb[0]) * se[0] + R(kZb[1]) * se[1];
-  res[0] = -sxt - set + R(0.5) * sz[0];
-  res[1] = sxt + R(0.5) * sz[1];
-  res[2] = set + R(0.5) * sz[2];
-  res[3] = -sxb - seb - R(0.5) * sz[0];
-  res[4] = sxb - R(0.5) * sz[1];
-  res[5] = seb - R(0.5) * sz[2];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    R sx[2], se[2], sz[3] = {R(0), R(0), R(0)};
+    R T[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) T[i] = own(f, i);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const R tk = R(kZt[k]), bk = R(kZb[k]);
+      R ta[3];
+#pragma unroll
+      for (int n = 0; n < 3; ++n) ta[n] = tk * T[n] + bk * T[n + 3];
+      sx[k] = ta[0] * Px[k][0] + ta[1] * Px[k][1] + ta[2] * Px[k][2];
+      se[k] = ta[0] * Pe[k][0] + ta[1] * Pe[k][1] + ta[2] * Pe[k][2];
+      sz[0] += G[k][0] * ta[0] + G[k][3] * ta[1] + G[k][4] * ta[2];
+      sz[1] += G[k][3] * ta[0] + G[k][1] * ta[1] + G[k][5] * ta[2];
+      sz[2] += G[k][4] * ta[0] + G[k][5] * ta[1] + G[k][2] * ta[2];
+    }
+    // dphi/dxi = dlambda/dxi * (t or b), dphi/dzeta = +-lambda/2
+    const R sxt = R(kZt[0]) * sx[0] + R(kZt[1]) * sx[1];
+    const R sxb = R(kZb[0]) * sx[0] + R(kZb[1]) * sx[1];
+    const R set = R(kZt[0]) * se[0] + R(kZt[1]) * se[1];
+    const R seb = R(kZb[0]) * se[0] + R(kZb[1]) * se[1];
+    res[f][0] = -sxt - set + R(0.5) * sz[0];
+    res[f][1] = sxt + R(0.5) * sz[1];
+    res[f][2] = set + R(0.5) * sz[2];
+    res[f][3] = -sxb - seb - R(0.5) * sz[0];
+    res[f][4] = sxb - R(0.5) * sz[1];
+    res[f][5] = seb - R(0.5) * sz[2];
+  }
 }
 
 // Lateral face e (edge A = e -> B = e+1) of a column: neighbour slot and
@@ -299,34 +307,24 @@ __device__ __forceinline__ void lat_nb(const StageArgs& a, const LatMeta<R>& M, 
   }
 }
 
-// Upwind weights at the 3 x 2 face points from q = u_n dS, u_n the normal
-// component of the average of the two velocity traces (a wall carries no
-// flux): the flux is q times the inner trace where q > 0, else the outer one.
+// Face weights q = u_n dS at the 3 x 2 face points (edge point j, zeta_k), u_n
+// the normal component of the average of the two velocity traces (a wall
+// carries no flux): the flux is q times the inner trace where q > 0, else the
+// outer one.
 template <typename R>
-struct LatF {
-  // FP64 keeps the signed weight q alone, and picks the upwind trace by its
-  // sign (the one wavefront per SIMD runs short of registers: 1.5-2% faster);
-  // FP32 keeps max(q, 0) and min(q, 0) (2% slower the other way).
-  static constexpr bool kSigned = sizeof(R) == 8;
-  R up[3][2];                    // q (FP64) or max(q, 0) (FP32)
-  R um[kSigned ? 1 : 3][2];      // min(q, 0) (FP32 only)
-  uint32_t no[4];
-  bool interior;
-  bool lds;
+struct LatQ {
+  R q[3][2];
 };
 
 template <typename R>
-__device__ __forceinline__ void lat_factors(const LatMeta<R>& M, const LatNb<R>& nb, int e, int l, const R dz[3],
-                                            const R u[6], const R v[6], LatF<R>& F) {
+__device__ __forceinline__ void lat_weights(const LatMeta<R>& M, const LatNb<R>& nb, int e, int l, const R dz[3],
+                                            const R u[6], const R v[6], LatQ<R>& F) {
   const int A = e, B = (e + 1) % 3;
-  F.interior = M.nslot >= 0;
-  const bool wall = F.interior && l >= (M.meta >> 2);
-  const bool live = F.interior && !wall;
+  const bool interior = M.nslot >= 0;
+  const bool wall = interior && l >= (M.meta >> 2);
+  const bool live = interior && !wall;
   const R nx = M.nx, ny = M.ny;
   const R Le = wall ? R(0) : M.Le;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) F.no[j] = nb.no[j];
-  F.lds = nb.lds;
   R un[4] = {nx * u[A] + ny * v[A], nx * u[B] + ny * v[B], nx * u[A + 3] + ny * v[A + 3],
              nx * u[B + 3] + ny * v[B + 3]};
 #pragma unroll
@@ -341,51 +339,85 @@ __device__ __forceinline__ void lat_factors(const LatMeta<R>& M, const LatNb<R>&
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const R tk = R(kZt[k]), bk = R(kZb[k]);
-      const R q = (s1 * (tk * un[0] + bk * un[2]) + s * (tk * un[1] + bk * un[3])) * dS;
-      if constexpr (LatF<R>::kSigned) {
-        F.up[j][k] = q;
-      } else {
-        F.up[j][k] = upos(q);
-        F.um[j][k] = uneg(q);
-      }
+      F.q[j][k] = (s1 * (tk * un[0] + bk * un[2]) + s * (tk * un[1] + bk * un[3])) * dS;
     }
   }
 }
 
-// The neighbour's 4 face-node values of field f (stage input), or the
-// exterior value on an open boundary.
+// The neighbour's face-node value (stage input), or the exterior value on an
+// open boundary.
 template <typename R>
-__device__ __forceinline__ void lat_neighbour(const StageArgs& a, const LatF<R>& F, int f, R to[4]) {
-  const R* fb = static_cast<const R*>(a.Ts) + (size_t)(f * 6) * (size_t)a.m.n_slots;
-  const R te = R(a.t_ext[f]);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const R x = ldb(fb, F.no[j]);
-    to[j] = F.interior ? x : te;
-  }
+__device__ __forceinline__ R lat_trace(const StageArgs& a, const LatMeta<R>& M, int f, R x) {
+  return M.nslot >= 0 ? x : R(a.t_ext[f]);
 }
 
-// res[i] -= int_face phi_i Fhat dS for one field.
-template <typename R>
-__device__ __forceinline__ void lat_field(int e, const LatF<R>& F, const R T[6], const R to[4], R res[6]) {
+// res[f][i] -= int_face phi_i Fhat dS of all fields; to[f]: the outer traces.
+// In float with two fields or more the sums over the points are contracted
+// first, for inflow and outflow, over zeta then along the edge, into the 4 x 4
+// matrices of the face nodes (9 distinct entries each), so a field takes 32
+// multiply-adds instead of about 80.  In double that is 2% faster for four
+// fields too, but the point form picks the upwind trace by the sign of q, and
+// so keeps a non-finite value out of the prisms upwind of it.
+template <typename R, int NF, typename Own>
+__device__ __forceinline__ void lat_apply(int e, const LatQ<R>& F, Own own, const R (&to)[NF][4], R (&res)[NF][6]) {
   const int A = e, B = (e + 1) % 3;
+  if constexpr (NF == 1 || sizeof(R) == 8) {
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const R s = R(kS[j]), s1 = R(1) - R(kS[j]);
+    for (int f = 0; f < NF; ++f) {
+      const R TA = own(f, A), TB = own(f, B), TA3 = own(f, A + 3), TB3 = own(f, B + 3);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const R tk = R(kZt[k]), bk = R(kZb[k]);
-      const R ti = s1 * (tk * T[A] + bk * T[A + 3]) + s * (tk * T[B] + bk * T[B + 3]);
-      const R tq = s1 * (tk * to[0] + bk * to[2]) + s * (tk * to[1] + bk * to[3]);
-      R fl;
-      if constexpr (LatF<R>::kSigned)
-        fl = F.up[j][k] * (F.up[j][k] > R(0) ? ti : tq);
-      else
-        fl = F.up[j][k] * ti + F.um[j][k] * tq;
-      res[A] -= s1 * tk * fl;
-      res[B] -= s * tk * fl;
-      res[A + 3] -= s1 * bk * fl;
-      res[B + 3] -= s * bk * fl;
+      for (int j = 0; j < 3; ++j) {
+        const R s = R(kS[j]), s1 = R(1) - R(kS[j]);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const R tk = R(kZt[k]), bk = R(kZb[k]);
+          const R ti = s1 * (tk * TA + bk * TA3) + s * (tk * TB + bk * TB3);
+          const R tq = s1 * (tk * to[f][0] + bk * to[f][2]) + s * (tk * to[f][1] + bk * to[f][3]);
+          const R fl = F.q[j][k] * (F.q[j][k] > R(0) ? ti : tq);
+          res[f][A] -= s1 * tk * fl;
+          res[f][B] -= s * tk * fl;
+          res[f][A + 3] -= s1 * bk * fl;
+          res[f][B + 3] -= s * bk * fl;
+        }
+      }
+    }
+  } else {
+    // K[x][y]: x = AA, AB, BB along the edge, y = top-top, top-bottom, bottom-bottom
+    R Kp[3][3], Km[3][3];
+    R gp[3][3], gm[3][3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const R p0 = upos(F.q[j][0]), p1 = upos(F.q[j][1]), m0 = uneg(F.q[j][0]), m1 = uneg(F.q[j][1]);
+      gp[j][0] = R(kZt[0] * kZt[0]) * p0 + R(kZt[1] * kZt[1]) * p1;
+      gp[j][1] = R(kZt[0] * kZb[0]) * p0 + R(kZt[1] * kZb[1]) * p1;
+      gp[j][2] = R(kZb[0] * kZb[0]) * p0 + R(kZb[1] * kZb[1]) * p1;
+      gm[j][0] = R(kZt[0] * kZt[0]) * m0 + R(kZt[1] * kZt[1]) * m1;
+      gm[j][1] = R(kZt[0] * kZb[0]) * m0 + R(kZt[1] * kZb[1]) * m1;
+      gm[j][2] = R(kZb[0] * kZb[0]) * m0 + R(kZb[1] * kZb[1]) * m1;
+    }
+#pragma unroll
+    for (int y = 0; y < 3; ++y) {
+      constexpr double s0 = kS[0], s2 = kS[2];
+      // edge points at s0, 1/2 and s2 = 1 - s0
+      Kp[0][y] = R(s2 * s2) * gp[0][y] + R(0.25) * gp[1][y] + R(s0 * s0) * gp[2][y];
+      Kp[1][y] = R(s0 * s2) * gp[0][y] + R(0.25) * gp[1][y] + R(s0 * s2) * gp[2][y];
+      Kp[2][y] = R(s0 * s0) * gp[0][y] + R(0.25) * gp[1][y] + R(s2 * s2) * gp[2][y];
+      Km[0][y] = R(s2 * s2) * gm[0][y] + R(0.25) * gm[1][y] + R(s0 * s0) * gm[2][y];
+      Km[1][y] = R(s0 * s2) * gm[0][y] + R(0.25) * gm[1][y] + R(s0 * s2) * gm[2][y];
+      Km[2][y] = R(s0 * s0) * gm[0][y] + R(0.25) * gm[1][y] + R(s2 * s2) * gm[2][y];
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const R TA = own(f, A), TB = own(f, B), TA3 = own(f, A + 3), TB3 = own(f, B + 3);
+      const R* o = to[f];
+      res[f][A] -= Kp[0][0] * TA + Kp[1][0] * TB + Kp[0][1] * TA3 + Kp[1][1] * TB3 +
+                   (Km[0][0] * o[0] + Km[1][0] * o[1] + Km[0][1] * o[2] + Km[1][1] * o[3]);
+      res[f][B] -= Kp[1][0] * TA + Kp[2][0] * TB + Kp[1][1] * TA3 + Kp[2][1] * TB3 +
+                   (Km[1][0] * o[0] + Km[2][0] * o[1] + Km[1][1] * o[2] + Km[2][1] * o[3]);
+      res[f][A + 3] -= Kp[0][1] * TA + Kp[1][1] * TB + Kp[0][2] * TA3 + Kp[1][2] * TB3 +
+                       (Km[0][1] * o[0] + Km[1][1] * o[1] + Km[0][2] * o[2] + Km[1][2] * o[3]);
+      res[f][B + 3] -= Kp[1][1] * TA + Kp[2][1] * TB + Kp[1][2] * TA3 + Kp[2][2] * TB3 +
+                       (Km[1][1] * o[0] + Km[2][1] * o[1] + Km[1][2] * o[2] + Km[2][2] * o[3]);
     }
   }
 }
@@ -588,72 +620,91 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile
     zb[v3] = ldb(zl + v3 * LS, (lt + kCell) * (uint32_t)sizeof(R));
     dz[v3] = zt[v3] - zb[v3];
   }
-  VolF<R> vf;
-  LatF<R> lf[3];
-  HorF<R> top, bot;
-  MinvF<R> mf;
-  {
-    R u[6], v[6], w[6];
+  R T[NF][6], res[NF][6];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      u[i] = ldr(U, S, 0 * 6 + i, po);
-      v[i] = ldr(U, S, 1 * 6 + i, po);
-      w[i] = WZ ? R(0) : ldr(U, S, 2 * 6 + i, po);
-    }
-    volume_factors<R, WZ>(cg, zt, zb, dz, u, v, w, vf);
+  for (int f = 0; f < NF; ++f)
 #pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      LatMeta<R> M;
-      LatNb<R> nb;
-      lat_meta<R>(m, e, co, M);
-      lat_nb<R>(a, M, e, l, po, nb);
-      lat_factors<R>(M, nb, e, l, dz, u, v, lf[e]);
-    }
-    R ux[3], vx[3], wx[3];
+    for (int i = 0; i < 6; ++i) T[f][i] = ldr(Ts, S, f * 6 + i, po);
+  auto own = [&](int f, int i) { return T[f][i]; };
+  R u[6], v[6], w[6];
 #pragma unroll
-    for (int n = 0; n < 3; ++n) {
-      ux[n] = ldr(U, S, 0 * 6 + 3 + n, pup);
-      vx[n] = ldr(U, S, 1 * 6 + 3 + n, pup);
-      wx[n] = WZ ? R(0) : ldr(U, S, 2 * 6 + 3 + n, pup);
-    }
-    hface_factors<R, WZ>(cg, zt, l > 0, ux, vx, wx, true, u, v, w, top);
-#pragma unroll
-    for (int n = 0; n < 3; ++n) {
-      ux[n] = ldr(U, S, 0 * 6 + n, plo);
-      vx[n] = ldr(U, S, 1 * 6 + n, plo);
-      wx[n] = WZ ? R(0) : ldr(U, S, 2 * 6 + n, plo);
-    }
-    hface_factors<R, WZ>(cg, zb, true, u + 3, v + 3, w + 3, l < N - 1, ux, vx, wx, bot);
-    minv_factors<R>(cg, dz, mf);
+  for (int i = 0; i < 6; ++i) {
+    u[i] = ldr(U, S, 0 * 6 + i, po);
+    v[i] = ldr(U, S, 1 * 6 + i, po);
+    w[i] = WZ ? R(0) : ldr(U, S, 2 * 6 + i, po);
   }
+  LatMeta<R> M[3];
+#pragma unroll
+  for (int e = 0; e < 3; ++e) lat_meta<R>(m, e, co, M[e]);
+  // A term's neighbour values are requested one term ahead of their use.
+  LatNb<R> nb[2];
+  R to[2][NF][4];
+  auto request = [&](int e) {
+    lat_nb<R>(a, M[e], e, l, po, nb[e & 1]);
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) to[e & 1][f][j] = ldb(Ts + (size_t)(f * 6) * S, nb[e & 1].no[j]);
+  };
+  R ut[2][9], Tx[2][NF][3];   // above (bottom nodes) and below (top nodes): velocity, stage input
+  auto request_layer = [&](int s, uint32_t pn) {
+    const int n0 = s == 0 ? 3 : 0;
+#pragma unroll
+    for (int n = 0; n < 3; ++n) {
+      ut[s][n] = ldr(U, S, 0 * 6 + n0 + n, pn);
+      ut[s][3 + n] = ldr(U, S, 1 * 6 + n0 + n, pn);
+      ut[s][6 + n] = WZ ? R(0) : ldr(U, S, 2 * 6 + n0 + n, pn);
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int n = 0; n < 3; ++n) Tx[s][f][n] = ldr(Ts, S, f * 6 + n0 + n, pn);
+  };
+  request(0);
+  phase();
+  volume_term<R, NF, WZ>(cg, zt, zb, dz, u, v, w, own, res);
+  formed<R, NF>(res);
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    if (e < 2) request(e + 1);
+    else request_layer(0, pup);
+    phase();
+    LatQ<R> F;
+    lat_weights<R>(M[e], nb[e & 1], e, l, dz, u, v, F);
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) to[e & 1][f][j] = lat_trace<R>(a, M[e], f, to[e & 1][f][j]);
+    lat_apply<R, NF>(e, F, own, to[e & 1], res);
+    formed<R, NF>(res);
+  }
+  request_layer(1, plo);
+  R tn[NF][6];
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int i = 0; i < 6; ++i) tn[f][i] = READ_TN ? ldr(Tn, S, f * 6 + i, po) : R(0);
+  phase();
+  HorF<R> hf;
+  hface_factors<R, WZ>(cg, zt, l > 0, ut[0], ut[0] + 3, ut[0] + 6, true, u, v, w, hf);
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    R T[6], res[6], tn[6];
+    R g[3];
+    hface_field<R>(hf, R(a.t_ext[f]), Tx[0][f], T[f], g);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      T[i] = ldr(Ts, S, f * 6 + i, po);
-      tn[i] = READ_TN ? ldr(Tn, S, f * 6 + i, po) : R(0);
-    }
-    volume_field<R>(vf, T, res);
+    for (int n = 0; n < 3; ++n) res[f][n] -= g[n];
+  }
+  formed<R, NF>(res);
+  hface_factors<R, WZ>(cg, zb, true, u + 3, v + 3, w + 3, l < N - 1, ut[1], ut[1] + 3, ut[1] + 6, hf);
+  MinvF<R> mf;
+  minv_factors<R>(cg, dz, mf);
 #pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      R to[4];
-      lat_neighbour<R>(a, lf[e], f, to);
-      lat_field<R>(e, lf[e], T, to, res);
-    }
-    const R te = R(a.t_ext[f]);
-    R Tx[3], g[3];
+  for (int f = 0; f < NF; ++f) {
+    R g[3];
+    hface_field<R>(hf, R(a.t_ext[f]), T[f] + 3, Tx[1][f], g);
 #pragma unroll
-    for (int n = 0; n < 3; ++n) Tx[n] = ldr(Ts, S, f * 6 + 3 + n, pup);
-    hface_field<R>(top, te, Tx, T, g);
-#pragma unroll
-    for (int n = 0; n < 3; ++n) res[n] -= g[n];
-#pragma unroll
-    for (int n = 0; n < 3; ++n) Tx[n] = ldr(Ts, S, f * 6 + n, plo);
-    hface_field<R>(bot, te, T + 3, Tx, g);
-#pragma unroll
-    for (int n = 0; n < 3; ++n) res[3 + n] += g[n];
-    finish_field<R, RHS, READ_TN, OUT2>(a, mf, f, T, res, tn, po, active);
+    for (int n = 0; n < 3; ++n) res[f][3 + n] += g[n];
+    finish_field<R, RHS, READ_TN, OUT2>(a, mf, f, T[f], res[f], tn[f], po, active);
   }
 }
 
@@ -800,22 +851,18 @@ __device__ __forceinline__ void lat_nb_walk(const StageArgs& a, const LatMeta<R>
   }
 }
 
-// Column-walk form of lat_neighbour: field f's neighbour traces from the LDS
-// slot or from global memory, as lat_nb_walk decided.
+// Column-walk form of the neighbour traces of field f: from the LDS slot or from
+// global memory, as lat_nb_walk decided.
 template <typename R, int kTsRow>
-__device__ __forceinline__ void lat_neighbour_walk(const StageArgs& a, const LatF<R>& F, int f, const R* cur,
-                                                   R to[4]) {
+__device__ __forceinline__ void lat_traces_walk(const StageArgs& a, const LatNb<R>& nb, int f, const R* cur, R to[4]) {
   const R* fb = static_cast<const R*>(a.Ts) + (size_t)(f * 6) * (size_t)a.m.n_slots;
-  const R te = R(a.t_ext[f]);
   constexpr uint32_t row = kCell * sizeof(R);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    R x;
-    if (F.lds)
-      x = lds_at(cur, (uint32_t)(kTsRow + f * 6) * row + F.no[j]);
+    if (nb.lds)
+      to[j] = lds_at(cur, (uint32_t)(kTsRow + f * 6) * row + nb.no[j]);
     else
-      x = ldb(fb, F.no[j]);
-    to[j] = F.interior ? x : te;
+      to[j] = ldb(fb, nb.no[j]);
   }
 }
 
@@ -829,9 +876,10 @@ struct WalkCarry {
 // One layer l of the walk.  `cur` holds layer l (complete), `nxt` receives
 // layer l+1.  cur and nxt are distinct __shared__ arrays, so the compiler
 // sees that reading cur does not wait for the copy into nxt.  Loads complete
-// in order, so each phase issues the loads it needs before the ones needed
-// later: neighbour velocities, then the next layer's copy, then (per field)
-// neighbour traces one field ahead.
+// in order, so the layer's loads are issued in the order of their use, all of
+// them before its arithmetic: the prism's own values (LDS), the neighbours'
+// velocities and traces, the next layer's copy, Tn.  Nothing but the bottom
+// face and the update then waits on the copy.
 template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2>
 __device__ __forceinline__ void walk_layer(const StageArgs& a, const ColGeo<R>& cg, const LatMeta<R> (&lm)[3],
                                            const WalkCell& wc, int lane, int l, const R* cur, R* nxt,
@@ -844,56 +892,80 @@ __device__ __forceinline__ void walk_layer(const StageArgs& a, const ColGeo<R>& 
   const uint32_t po = p * (uint32_t)sizeof(R);
   const bool below = l + 1 < depth;   // wavefront-uniform
   const bool active = l < N;
-  auto own = [&](int row) { return cur[row * kCell + lane]; };
+  auto at = [&](int row) { return cur[row * kCell + lane]; };
   auto next = [&](int row, R fallback) { return below ? nxt[row * kCell + lane] : fallback; };
 
-  // In-cell neighbours from LDS: 1.8% faster over a step's three stages in
-  // FP64, 9% in FP32 (with two wavefronts per SIMD resident).
+  R T[NF][6], u[6], v[6], w[6], zb[3], dz[3];
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int i = 0; i < 6; ++i) T[f][i] = at(Ly::kTs + f * 6 + i);
+  auto held = [&](int f, int i) { return T[f][i]; };
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    u[i] = at(Ly::kU + i);
+    v[i] = at(Ly::kU + 6 + i);
+    w[i] = WZ ? R(0) : at(Ly::kU + 12 + i);
+  }
+#pragma unroll
+  for (int v3 = 0; v3 < 3; ++v3) {
+    zb[v3] = at(Ly::kZ + v3);
+    dz[v3] = cs.zt[v3] - zb[v3];
+  }
+  // the neighbour reads below are flat loads, which count against both wait
+  // counters: an LDS read still in flight would make its user wait for them too
+  wait_lgkm();
+  phase();
   LatNb<R> nb[3];
+  R to[3][NF][4];
 #pragma unroll
   for (int e = 0; e < 3; ++e) lat_nb_walk<R, Ly::kU>(a, lm[e], e, l, po, lane, wc.base, cur, nb[e]);
-  wait_lgkm();
+#pragma unroll
+  for (int e = 0; e < 3; ++e)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) lat_traces_walk<R, Ly::kTs>(a, nb[e], f, cur, to[e][f]);
+  phase();
   if (below) walk_fetch<R, NF, WZ, READ_TN>(a, wc, l + 1, nxt, lane);
   mem_order();
   phase();
 
-  R zb[3], dz[3];
+  R res[NF][6];
+  volume_term<R, NF, WZ>(cg, cs.zt, zb, dz, u, v, w, held, res);
+  formed<R, NF>(res);
+  // from here on the prism's own values are read from LDS again: the first use
+  // of a neighbour value waits for all of them, and LDS reads no longer wait
+  mem_order();
+  auto own = [&](int f, int i) { return at(Ly::kTs + f * 6 + i); };
+  const R* __restrict__ Tn = static_cast<const R*>(a.Tn);
+  R tn[NF][6];
 #pragma unroll
-  for (int v3 = 0; v3 < 3; ++v3) {
-    zb[v3] = own(Ly::kZ + v3);
-    dz[v3] = cs.zt[v3] - zb[v3];
+  for (int e = 0; e < 3; ++e) {
+    LatQ<R> F;
+    lat_weights<R>(lm[e], nb[e], e, l, dz, u, v, F);
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) to[e][f][j] = lat_trace<R>(a, lm[e], f, to[e][f][j]);
+    lat_apply<R, NF>(e, F, own, to[e], res);
+    formed<R, NF>(res);
+    if (e == 1) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int i = 0; i < 6; ++i) tn[f][i] = (READ_TN && !Ly::kTnLds) ? ldr(Tn, S, f * 6 + i, po) : R(0);
+      phase();
+    }
   }
-  VolF<R> vf;
-  LatF<R> lf[3];
-  HorF<R> bot;
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int n = 0; n < 3; ++n) res[f][n] -= cs.gtop[f][n];
   MinvF<R> mf;
-  // Neighbour traces are requested kTA fields ahead of the field being
-  // computed: two in FP64 (2.8% faster over a step's three stages, the
-  // cross-cell gathers' latency being the longest), one in FP32 (2-4% slower
-  // with two).
-  constexpr int kTA = (sizeof(R) == 8 && NF > 2) ? 2 : 1;
-  R to[3][4], to1[3][4];
+  minv_factors<R>(cg, dz, mf);
+  phase();
+  wait_vm();   // layer l+1 has arrived
+  HorF<R> bot;
   {
-    R u[6], v[6], w[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      u[i] = own(Ly::kU + i);
-      v[i] = own(Ly::kU + 6 + i);
-      w[i] = WZ ? R(0) : own(Ly::kU + 12 + i);
-    }
-    volume_factors<R, WZ>(cg, cs.zt, zb, dz, u, v, w, vf);
-    minv_factors<R>(cg, dz, mf);
-    phase();
-#pragma unroll
-    for (int e = 0; e < 3; ++e) lat_factors<R>(lm[e], nb[e], e, l, dz, u, v, lf[e]);
-#pragma unroll
-    for (int e = 0; e < 3; ++e) lat_neighbour_walk<R, Ly::kTs>(a, lf[e], 0, cur, to[e]);
-    if (kTA == 2) {
-#pragma unroll
-      for (int e = 0; e < 3; ++e) lat_neighbour_walk<R, Ly::kTs>(a, lf[e], 1, cur, to1[e]);
-    }
-    phase();
-    wait_vm();   // layer l+1 has arrived
     R ul[3], vl[3], wl[3];
 #pragma unroll
     for (int n = 0; n < 3; ++n) {
@@ -903,61 +975,22 @@ __device__ __forceinline__ void walk_layer(const StageArgs& a, const ColGeo<R>& 
     }
     hface_factors<R, WZ>(cg, zb, true, u + 3, v + 3, w + 3, l < N - 1, ul, vl, wl, bot);
   }
-  const R* __restrict__ Tn = static_cast<const R*>(a.Tn);
-  R tn[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-    tn[i] = (READ_TN && !Ly::kTnLds) ? ldr(Tn, S, i, po) : R(0);
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     phase();
-    R T[6], res[6], ton[3][4], tnn[6];
-    // neighbour traces kTA fields ahead, and the next field's Tn, are
-    // requested before this field computes
-    if (f + kTA < NF) {
+    R Tl[3], Tf[6];
 #pragma unroll
-      for (int e = 0; e < 3; ++e) lat_neighbour_walk<R, Ly::kTs>(a, lf[e], f + kTA, cur, ton[e]);
-    }
-    if (f + 1 < NF) {
+    for (int i = 0; i < 6; ++i) Tf[i] = own(f, i);
 #pragma unroll
-      for (int i = 0; i < 6; ++i)
-        tnn[i] = (READ_TN && !Ly::kTnLds) ? ldr(Tn, S, (f + 1) * 6 + i, po) : R(0);
-    }
+    for (int n = 0; n < 3; ++n) Tl[n] = next(Ly::kTs + f * 6 + n, Tf[3 + n]);
+    hface_field<R>(bot, R(a.t_ext[f]), Tf + 3, Tl, cs.gtop[f]);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) T[i] = own(Ly::kTs + f * 6 + i);
-    volume_field<R>(vf, T, res);
-#pragma unroll
-    for (int e = 0; e < 3; ++e) lat_field<R>(e, lf[e], T, to[e], res);
-#pragma unroll
-    for (int n = 0; n < 3; ++n) res[n] -= cs.gtop[f][n];
-    {
-      R Tl[3];
-#pragma unroll
-      for (int n = 0; n < 3; ++n) Tl[n] = next(Ly::kTs + f * 6 + n, T[3 + n]);
-      hface_field<R>(bot, R(a.t_ext[f]), T + 3, Tl, cs.gtop[f]);
-#pragma unroll
-      for (int n = 0; n < 3; ++n) res[3 + n] += cs.gtop[f][n];
-    }
+    for (int n = 0; n < 3; ++n) res[f][3 + n] += cs.gtop[f][n];
     if (Ly::kTnLds) {
 #pragma unroll
-      for (int i = 0; i < 6; ++i) tn[i] = own(Ly::kTn + f * 6 + i);
+      for (int i = 0; i < 6; ++i) tn[f][i] = at(Ly::kTn + f * 6 + i);
     }
-    finish_field<R, RHS, READ_TN, OUT2>(a, mf, f, T, res, tn, po, active);
-    if (f + 1 < NF) {
-#pragma unroll
-      for (int e = 0; e < 3; ++e)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (kTA == 2) {
-            to[e][j] = to1[e][j];
-            to1[e][j] = ton[e][j];
-          } else {
-            to[e][j] = ton[e][j];
-          }
-        }
-#pragma unroll
-      for (int i = 0; i < 6; ++i) tn[i] = tnn[i];
-    }
+    finish_field<R, RHS, READ_TN, OUT2>(a, mf, f, Tf, res[f], tn[f], po, active);
   }
 #pragma unroll
   for (int v3 = 0; v3 < 3; ++v3) cs.zt[v3] = zb[v3];
