@@ -89,8 +89,18 @@ __device__ __forceinline__ void formed(double (&res)[NF][6]) {
 // ahead: the kernel is bound by the latency of its loads at two wavefronts per
 // SIMD.  Against loads behind branches per face, each waiting on its own:
 // 18.8 -> 11.3 us (2 fields, 55 k prisms), 91.7 -> 84.3 us (1 field, 1.0 M prisms).
-template <int NF, bool WZ>
+// With SH each wavefront puts its layer's Y and horizontal velocity in LDS, reads
+// them again from there for each term, and with them its neighbours in the cell:
+// the address unit of the loads is then no longer the bound of a large launch, where
+// a neighbour gather costs it five times a row of the own prisms.
+template <int NF>
+constexpr int kAdjRows = 6 * NF + 12;   // LDS rows of a wavefront: Y, u, v
+
+template <int NF, bool WZ, bool SH>
 __global__ __launch_bounds__(256) void adj_stage_kernel(AdjStageArgs a) {
+  // each wavefront's own rows: its LDS accesses complete in order, no barrier needed
+  extern __shared__ __align__(16) char adj_lds[];
+  double* sh = SH ? reinterpret_cast<double*>(adj_lds) + (threadIdx.x >> 6) * (kAdjRows<NF> * kCell) : nullptr;
   const DevMesh& m = a.m;
   const WgTile tile = a.tiles[a.xcd ? xcd_tile(blockIdx.x, a.n_tiles) : (int)blockIdx.x];
   const int lane = threadIdx.x & (kCell - 1);
@@ -143,28 +153,66 @@ __global__ __launch_bounds__(256) void adj_stage_kernel(AdjStageArgs a) {
     for (int i = 0; i < 6; ++i) yv[f][i] = ldr(Y, S, f * 6 + i, po);
 
   // lateral face e: the neighbour's velocity and Y at the face nodes A top, B top,
-  // A bottom, B bottom, and the face's normal and length
+  // A bottom, B bottom, and the face's normal and length; with SH a neighbour in the
+  // cell (here) is read from LDS at the time of its use, at offsets lo
   double nu[2][4], nv[2][4], ny4[2][NF][4], fn[2][3];
+  uint32_t lo[2][2];
+  bool here[2];
+  const uint32_t cell_base = (uint32_t)m.cell_base[tile.cell];
   auto request_face = [&](int e) {
     const int s = e & 1;
     const bool live = nslots[e] >= 0 && l < (metas[e] >> 2);
     const int kp = metas[e] & 3;
     const uint32_t nA = live ? (uint32_t)((kp + 1) % 3) : (uint32_t)e;
     const uint32_t nB = live ? (uint32_t)kp : (uint32_t)((e + 1) % 3);
+    const uint32_t nl = (uint32_t)nslots[e] - cell_base;   // < 64 iff the neighbour is in this cell
+    here[s] = SH && (!live || nl < (uint32_t)kCell);
+    const uint32_t src = live ? nl : (uint32_t)lane;
+    lo[s][0] = here[s] ? nA * kCell + src : 0u;
+    lo[s][1] = here[s] ? nB * kCell + src : 0u;
     const uint32_t pno = live ? ((uint32_t)nslots[e] + (uint32_t)l * kCell) * 8u : po;
     const uint32_t no[4] = {nA * rs + pno, nB * rs + pno, (nA + 3u) * rs + pno, (nB + 3u) * rs + pno};
     fn[s][0] = ld(geo + (G_NX + e) * CS, co);
     fn[s][1] = ld(geo + (G_NY + e) * CS, co);
     fn[s][2] = ld(geo + (G_LE + e) * CS, co);
+    if (!here[s]) {
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        nu[s][n] = ld(U, no[n]);
+        nv[s][n] = ld(U + 6 * S, no[n]);
+      }
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) ny4[s][f][n] = ld(Y + (size_t)(f * 6) * S, no[n]);
+    }
+  };
+  auto resolve_face = [&](int s) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      nu[s][n] = ld(U, no[n]);
-      nv[s][n] = ld(U + 6 * S, no[n]);
+      const uint32_t o = lo[s][n & 1] + (uint32_t)(n >> 1) * 3u * kCell;
+      const double x = sh[6 * NF * kCell + o], y = sh[(6 * NF + 6) * kCell + o];
+      nu[s][n] = here[s] ? x : nu[s][n];
+      nv[s][n] = here[s] ? y : nv[s][n];
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const double t = sh[f * 6 * kCell + o];
+        ny4[s][f][n] = here[s] ? t : ny4[s][f][n];
+      }
     }
+  };
+  // with SH the own values are read from LDS again for each term
+  auto reread = [&]() {
+    if constexpr (SH) {
+      asm volatile("" ::: "memory");
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
+      for (int i = 0; i < 6; ++i) {
+        u[i] = sh[(6 * NF + i) * kCell + lane];
+        v[i] = sh[(6 * NF + 6 + i) * kCell + lane];
 #pragma unroll
-      for (int n = 0; n < 4; ++n) ny4[s][f][n] = ld(Y + (size_t)(f * 6) * S, no[n]);
+        for (int f = 0; f < NF; ++f) yv[f][i] = sh[(f * 6 + i) * kCell + lane];
+      }
+    }
   };
   // the layer above (side 0, its bottom nodes) or below (side 1, its top nodes)
   double nw[2][9], ny3[2][NF][3];
@@ -184,6 +232,16 @@ __global__ __launch_bounds__(256) void adj_stage_kernel(AdjStageArgs a) {
   };
   request_face(0);
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (SH) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) sh[(f * 6 + i) * kCell + lane] = yv[f][i];
+      sh[(6 * NF + i) * kCell + lane] = u[i];
+      sh[(6 * NF + 6 + i) * kCell + lane] = v[i];
+    }
+    asm volatile("" ::: "memory");
+  }
 
   // ---- volume: int phi_j U.grad(y_h) ----
   // sum over the points of w_q lambda_n x y for x, y linear over the triangle, by
@@ -250,6 +308,8 @@ __global__ __launch_bounds__(256) void adj_stage_kernel(AdjStageArgs a) {
     else request_layer(0);
     __builtin_amdgcn_sched_barrier(0);
     const int A = e, B = (e + 1) % 3, s2 = e & 1;
+    if constexpr (SH) resolve_face(s2);
+    reread();
     const bool interior = nslots[e] >= 0;
     const bool wall = interior && l >= (metas[e] >> 2);
     const double nx = fn[s2][0], ny = fn[s2][1];
@@ -319,6 +379,7 @@ __global__ __launch_bounds__(256) void adj_stage_kernel(AdjStageArgs a) {
         else x2[f][i] = a.X2 ? ldr(a.X2, S, f * 6 + i, po) : 0.0;
       }
     __builtin_amdgcn_sched_barrier(0);
+    reread();
     const int o = side == 0 ? 0 : 3;
     const bool has_nb = side == 0 ? (l > 0) : (l < N - 1);
     const double* zf = side == 0 ? zt : zb;
@@ -361,6 +422,7 @@ __global__ __launch_bounds__(256) void adj_stage_kernel(AdjStageArgs a) {
   if (l >= N) return;
 
   // ---- M^-1 and the combination ----
+  reread();
   const double m00 = 3.0 * dz[0] + dz[1] + dz[2];
   const double m11 = dz[0] + 3.0 * dz[1] + dz[2];
   const double m22 = dz[0] + dz[1] + 3.0 * dz[2];
@@ -967,17 +1029,27 @@ __global__ __launch_bounds__(64) void mdot_column_kernel(DevMesh m, const R* X, 
 }
 
 template <int NF>
-hipError_t launch_adj_stage_nf(const AdjStageArgs& a, bool w_zero, int tile_layers, hipStream_t s) {
-  dim3 grid(a.n_tiles), block(kCell * tile_layers);
-  if (w_zero) hipLaunchKernelGGL((adj_stage_kernel<NF, true>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((adj_stage_kernel<NF, false>), grid, block, 0, s, a);
+hipError_t launch_adj_stage_nf(const AdjStageArgs& a, bool w_zero, int tile_layers, int n_cu, hipStream_t s) {
+  const dim3 grid(a.n_tiles), block(kCell * tile_layers);
+  // more than 16 wavefronts per CU: neighbours in the cell through LDS.  Reverse step
+  // (three of these kernels and a solve), without -> with LDS, FP64: 15602 wavefronts 1
+  // field 317 -> 288 us, 2 fields 492 -> 437, 4 fields 851 -> 808; 4050 wavefronts 88.6
+  // -> 87.4, 121 -> 120, 195 -> 200; 897 wavefronts 37.5 -> 39.7, 48.8 -> 50.2, 66 -> 67.
+  if ((int64_t)a.n_tiles * tile_layers > 16 * (int64_t)n_cu) {
+    const size_t lds = block.x * kAdjRows<NF> * sizeof(double);
+    if (w_zero) hipLaunchKernelGGL((adj_stage_kernel<NF, true, true>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((adj_stage_kernel<NF, false, true>), grid, block, lds, s, a);
+  } else {
+    if (w_zero) hipLaunchKernelGGL((adj_stage_kernel<NF, true, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((adj_stage_kernel<NF, false, false>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_adjoint_stage(const DevMesh& m, const WgTile* tiles, int n_tiles, int tile_layers, int xcd,
-                                int n_fields, bool w_zero, const double* Y, const double* X1, const double* X2,
+                                int n_cu, int n_fields, bool w_zero, const double* Y, const double* X1, const double* X2,
                                 double* out, const double* U, double dt, double b, double a1, double a2,
                                 hipStream_t s) {
   if (n_tiles == 0) return hipSuccess;
@@ -996,10 +1068,10 @@ hipError_t launch_adjoint_stage(const DevMesh& m, const WgTile* tiles, int n_til
   a.a1 = a1;
   a.a2 = a2;
   switch (n_fields) {
-    case 1: return launch_adj_stage_nf<1>(a, w_zero, tile_layers, s);
-    case 2: return launch_adj_stage_nf<2>(a, w_zero, tile_layers, s);
-    case 3: return launch_adj_stage_nf<3>(a, w_zero, tile_layers, s);
-    case 4: return launch_adj_stage_nf<4>(a, w_zero, tile_layers, s);
+    case 1: return launch_adj_stage_nf<1>(a, w_zero, tile_layers, n_cu, s);
+    case 2: return launch_adj_stage_nf<2>(a, w_zero, tile_layers, n_cu, s);
+    case 3: return launch_adj_stage_nf<3>(a, w_zero, tile_layers, n_cu, s);
+    case 4: return launch_adj_stage_nf<4>(a, w_zero, tile_layers, n_cu, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -1332,15 +1332,15 @@ sdg_status sdg_step_adjoint(sdg_ctx* ctx, const void* dev_z_next, void* dev_z_ou
   // the horizontal diffusion D is symmetric, so its part of M^-1 (R_lin + D)^T
   // is M^-1 D, added to each stage as in the forward step
   const double dt = ctx->dt;
-  e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, P.F, wz, mu, nullptr, nullptr, zb2, U, dt,
+  e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, ctx->n_cu, P.F, wz, mu, nullptr, nullptr, zb2, U, dt,
                            2.0 / 3.0, 0.0, 0.0, s);
   if (e == hipSuccess) e = enqueue_hdiff(ctx, mu, zb2, nullptr, 2.0 / 3.0 * dt, 0.0, s);
   if (e == hipSuccess)
-    e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, P.F, wz, zb2, nullptr, nullptr, zb1, U, dt,
+    e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, ctx->n_cu, P.F, wz, zb2, nullptr, nullptr, zb1, U, dt,
                              0.25, 0.0, 0.0, s);
   if (e == hipSuccess) e = enqueue_hdiff(ctx, zb2, zb1, nullptr, 0.25 * dt, 0.0, s);
   if (e == hipSuccess)
-    e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, P.F, wz, zb1, mu, zb2, mu, U, dt, 1.0,
+    e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, ctx->n_cu, P.F, wz, zb1, mu, zb2, mu, U, dt, 1.0,
                              1.0 / 3.0, 0.75, s);
   if (e == hipSuccess) e = enqueue_hdiff(ctx, zb1, mu, nullptr, dt, 0.0, s);
   if (e != hipSuccess) return hip_fail(e, "adjoint stage launch");
@@ -1395,7 +1395,7 @@ sdg_status adjoint_imex(sdg_ctx* ctx, const char* who, const void* dev_z_next, v
     if ((st = enqueue_solve(ctx, dev_z_out, dev_z_out, h, s)) != SDG_OK) return st;
   }
   // w = 2 (Z1 + h L~ Z1)
-  e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, P.F, wz, Z1, nullptr, nullptr, w, U, h, 2.0, 0.0,
+  e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, ctx->n_cu, P.F, wz, Z1, nullptr, nullptr, w, U, h, 2.0, 0.0,
                            0.0, s);
   if (e == hipSuccess) e = enqueue_hdiff(ctx, Z1, w, nullptr, 2.0 * h, 0.0, s);
   // mu' = (M - h A^T)^-1 M w;  dJ/dkappa_l += h mu'^T A_l x_h
@@ -1409,7 +1409,7 @@ sdg_status adjoint_imex(sdg_ctx* ctx, const char* who, const void* dev_z_next, v
                               dev_dkappa, s);
   // Z0 = mu' + h L~ mu' + Z1 - w
   if (e == hipSuccess)
-    e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, P.F, wz, mu, Z1, w, out, U, h, 1.0, 1.0, -1.0, s);
+    e = launch_adjoint_stage(ctx->dm, tiles, nt, tl, xcd, ctx->n_cu, P.F, wz, mu, Z1, w, out, U, h, 1.0, 1.0, -1.0, s);
   if (e == hipSuccess) e = enqueue_hdiff(ctx, mu, out, nullptr, h, 0.0, s);
   if (e != hipSuccess) return hip_fail(e, "split-IMEX adjoint launch");
   g_err.clear();

@@ -192,7 +192,7 @@ hipError_t launch_finite_check(const DevMesh& m, const void* T, int n_fields, bo
 
 // Adjoint (FP64 only).
 hipError_t launch_adjoint_stage(const DevMesh& m, const WgTile* tiles, int n_tiles, int tile_layers, int xcd,
-                                int n_fields, bool w_zero, const double* Y, const double* X1, const double* X2,
+                                int n_cu, int n_fields, bool w_zero, const double* Y, const double* X1, const double* X2,
                                 double* out, const double* U, double dt, double b, double a1, double a2,
                                 hipStream_t s);
 // factor = true: compute and keep the transposed block-Thomas factors G_l for

@@ -280,7 +280,7 @@ template <typename R>
 struct LatNb {
   uint32_t no[4];
   R uo[4], vo[4];
-  bool lds;          // column walk: no[] are offsets into the layer's LDS slot
+  bool lds;          // no[] are offsets into the layer's rows in LDS (the neighbour is in the cell)
 };
 
 template <typename R>
@@ -304,6 +304,77 @@ __device__ __forceinline__ void lat_nb(const StageArgs& a, const LatMeta<R>& M, 
   for (int j = 0; j < 4; ++j) {
     nb.uo[j] = ldb(U, nb.no[j]);
     nb.vo[j] = ldb(U + 6 * S, nb.no[j]);
+  }
+}
+
+template <typename R>
+__device__ __forceinline__ R lds_at(const R* slot, uint32_t byte_off) {
+  return *reinterpret_cast<const R*>(reinterpret_cast<const char*>(slot) + byte_off);
+}
+
+// Keeps later LDS reads below a just-issued copy or store (compiler barrier only).
+__device__ __forceinline__ void mem_order() { asm volatile("" ::: "memory"); }
+
+// The request of the one-thread-per-prism kernel: the neighbour's velocity and stage
+// input, ahead of their use.  With SH a neighbour in the cell is not requested: the
+// wavefront holds its layer's rows of all 64 columns in LDS (stage input from row 0,
+// u from row 6 NF, v after it), and lat_resolve reads them from there at the time of
+// their use.  A face without a live neighbour then points at the own rows.
+template <typename R, int NF, bool SH>
+__device__ __forceinline__ void lat_request(const StageArgs& a, const LatMeta<R>& M, int e, int l, uint32_t po,
+                                            int lane, uint32_t cell_base, LatNb<R>& nb, R (&to)[NF][4]) {
+  const size_t S = (size_t)a.m.n_slots;
+  const R* __restrict__ Ts = static_cast<const R*>(a.Ts);
+  if constexpr (!SH) {
+    lat_nb<R>(a, M, e, l, po, nb);
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) to[f][j] = ldb(Ts + (size_t)(f * 6) * S, nb.no[j]);
+  } else {
+    const bool live = M.nslot >= 0 && l < (M.meta >> 2);
+    const int kp = M.meta & 3;
+    const uint32_t nl = (uint32_t)M.nslot - cell_base;   // < 64 iff the neighbour is in this cell
+    nb.lds = !live || nl < (uint32_t)kCell;
+    const uint32_t nA = live ? (uint32_t)((kp + 1) % 3) : (uint32_t)e;
+    const uint32_t nB = live ? (uint32_t)kp : (uint32_t)((e + 1) % 3);
+    const uint32_t src = live && nb.lds ? nl : (uint32_t)lane;
+    constexpr uint32_t row = kCell * sizeof(R);
+    nb.no[0] = nA * row + src * (uint32_t)sizeof(R);
+    nb.no[1] = nB * row + src * (uint32_t)sizeof(R);
+    nb.no[2] = nb.no[0] + 3u * row;
+    nb.no[3] = nb.no[1] + 3u * row;
+    if (!nb.lds) {
+      const uint32_t rs = (uint32_t)(S * sizeof(R));     // bytes per node row
+      const R* __restrict__ U = static_cast<const R*>(a.U);
+      const uint32_t pno = ((uint32_t)M.nslot + (uint32_t)l * kCell) * (uint32_t)sizeof(R);
+      const uint32_t go[4] = {nA * rs + pno, nB * rs + pno, (nA + 3u) * rs + pno, (nB + 3u) * rs + pno};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        nb.uo[j] = ldb(U, go[j]);
+        nb.vo[j] = ldb(U + 6 * S, go[j]);
+      }
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) to[f][j] = ldb(Ts + (size_t)(f * 6) * S, go[j]);
+    }
+  }
+}
+
+template <typename R, int NF>
+__device__ __forceinline__ void lat_resolve(const R* sh, LatNb<R>& nb, R (&to)[NF][4]) {
+  constexpr uint32_t row = kCell * sizeof(R);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const R x = lds_at(sh, 6 * NF * row + nb.no[j]), y = lds_at(sh, (6 * NF + 6) * row + nb.no[j]);
+    nb.uo[j] = nb.lds ? x : nb.uo[j];
+    nb.vo[j] = nb.lds ? y : nb.vo[j];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const R t = lds_at(sh, f * 6 * row + nb.no[j]);
+      to[f][j] = nb.lds ? t : to[f][j];
+    }
   }
 }
 
@@ -584,8 +655,23 @@ __device__ __forceinline__ TileRange tile_range(const StageArgs& a) {
 // ===========================================================================
 // stage_kernel: one thread per prism.
 // ===========================================================================
-template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2>
-__device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile) {
+// With SH each wavefront puts its layer's stage input and horizontal velocity in LDS,
+// reads them again from there for each term, and with them its neighbours in the
+// cell.  Without, the kernel is bound by the address unit of the loads, busy for 0.8
+// of the time: a neighbour gather touches about 45 lines where a row of the own
+// prisms touches 8.  With, four fields in double take 247 registers for 372 (two
+// wavefronts per SIMD for one).  Third stage, without -> with: FP64 4 fields 6.0 M
+// prisms 1.49 -> 1.22 ms, FP32 4 fields 0.80 -> 0.66 ms, FP64 1 field 1.0 M 93 ->
+// 79 us, FP64 3 fields with w 0.35 M 68 -> 61 us.  A launch of at most one wavefront
+// per SIMD has only its own chain of latencies, to which LDS adds: 281 wavefronts,
+// FP64 2 fields 7.3 -> 8.4 us, 897 wavefronts 12.4 -> 13.5 us, FP64 4 fields 14.8 ->
+// 18.9 us; from 1462 on every form is as fast or faster with LDS (22.7 for 26.1 us
+// there).  launch_mode draws the line at one wavefront per SIMD.
+template <int NF>
+constexpr int kStageRows = 6 * NF + 12;   // LDS rows of a wavefront: stage input, u, v
+
+template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2, bool SH>
+__device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile, R* sh) {
   const DevMesh& m = a.m;
   const int lane = threadIdx.x & (kCell - 1);
   const int l = tile.layer0 + (threadIdx.x >> 6);
@@ -625,7 +711,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile
   for (int f = 0; f < NF; ++f)
 #pragma unroll
     for (int i = 0; i < 6; ++i) T[f][i] = ldr(Ts, S, f * 6 + i, po);
-  auto own = [&](int f, int i) { return T[f][i]; };
+  auto held = [&](int f, int i) { return T[f][i]; };
+  auto own = [&](int f, int i) { return SH ? sh[(f * 6 + i) * kCell + lane] : T[f][i]; };
   R u[6], v[6], w[6];
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
@@ -636,15 +723,23 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile
   LatMeta<R> M[3];
 #pragma unroll
   for (int e = 0; e < 3; ++e) lat_meta<R>(m, e, co, M[e]);
+  // the velocity again for the next term
+  auto reread = [&]() {
+    if constexpr (SH) {
+      mem_order();
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        u[i] = sh[(6 * NF + i) * kCell + lane];
+        v[i] = sh[(6 * NF + 6 + i) * kCell + lane];
+      }
+    }
+  };
   // A term's neighbour values are requested one term ahead of their use.
   LatNb<R> nb[2];
   R to[2][NF][4];
+  const uint32_t cell_base = (uint32_t)m.cell_base[tile.cell];
   auto request = [&](int e) {
-    lat_nb<R>(a, M[e], e, l, po, nb[e & 1]);
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) to[e & 1][f][j] = ldb(Ts + (size_t)(f * 6) * S, nb[e & 1].no[j]);
+    lat_request<R, NF, SH>(a, M[e], e, l, po, lane, cell_base, nb[e & 1], to[e & 1]);
   };
   R ut[2][9], Tx[2][NF][3];   // above (bottom nodes) and below (top nodes): velocity, stage input
   auto request_layer = [&](int s, uint32_t pn) {
@@ -662,14 +757,27 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile
   };
   request(0);
   phase();
-  volume_term<R, NF, WZ>(cg, zt, zb, dz, u, v, w, own, res);
+  if constexpr (SH) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) sh[(f * 6 + i) * kCell + lane] = T[f][i];
+      sh[(6 * NF + i) * kCell + lane] = u[i];
+      sh[(6 * NF + 6 + i) * kCell + lane] = v[i];
+    }
+    mem_order();
+  }
+  volume_term<R, NF, WZ>(cg, zt, zb, dz, u, v, w, held, res);
   formed<R, NF>(res);
+  if constexpr (SH) mem_order();
 #pragma unroll
   for (int e = 0; e < 3; ++e) {
     if (e < 2) request(e + 1);
     else request_layer(0, pup);
     phase();
+    if constexpr (SH) lat_resolve<R, NF>(sh, nb[e & 1], to[e & 1]);
     LatQ<R> F;
+    reread();
     lat_weights<R>(M[e], nb[e & 1], e, l, dz, u, v, F);
 #pragma unroll
     for (int f = 0; f < NF; ++f)
@@ -686,32 +794,41 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile
     for (int i = 0; i < 6; ++i) tn[f][i] = READ_TN ? ldr(Tn, S, f * 6 + i, po) : R(0);
   phase();
   HorF<R> hf;
+  reread();
   hface_factors<R, WZ>(cg, zt, l > 0, ut[0], ut[0] + 3, ut[0] + 6, true, u, v, w, hf);
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
+    const R To[3] = {own(f, 0), own(f, 1), own(f, 2)};
     R g[3];
-    hface_field<R>(hf, R(a.t_ext[f]), Tx[0][f], T[f], g);
+    hface_field<R>(hf, R(a.t_ext[f]), Tx[0][f], To, g);
 #pragma unroll
     for (int n = 0; n < 3; ++n) res[f][n] -= g[n];
   }
   formed<R, NF>(res);
+  reread();
   hface_factors<R, WZ>(cg, zb, true, u + 3, v + 3, w + 3, l < N - 1, ut[1], ut[1] + 3, ut[1] + 6, hf);
   MinvF<R> mf;
   minv_factors<R>(cg, dz, mf);
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    R g[3];
-    hface_field<R>(hf, R(a.t_ext[f]), T[f] + 3, Tx[1][f], g);
+    R g[3], To[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) To[i] = own(f, i);
+    hface_field<R>(hf, R(a.t_ext[f]), To + 3, Tx[1][f], g);
 #pragma unroll
     for (int n = 0; n < 3; ++n) res[f][3 + n] += g[n];
-    finish_field<R, RHS, READ_TN, OUT2>(a, mf, f, T[f], res[f], tn[f], po, active);
+    finish_field<R, RHS, READ_TN, OUT2>(a, mf, f, To, res[f], tn[f], po, active);
   }
 }
 
-template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2>
+template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2, bool SH>
 __global__ __launch_bounds__(256) void stage_kernel(StageArgs a) {
+  // each wavefront's own rows: the LDS accesses of a wavefront complete in order, so
+  // they need no barrier, neither within a tile nor from one tile to the next
+  extern __shared__ __align__(16) char stage_lds[];
+  R* sh = SH ? reinterpret_cast<R*>(stage_lds) + (threadIdx.x >> 6) * (kStageRows<NF> * kCell) : nullptr;
   TileRange r = tile_range(a);
-  for (; r.t < r.end; r.t += r.step) stage_tile<R, NF, WZ, RHS, READ_TN, OUT2>(a, a.tiles[r.t]);
+  for (; r.t < r.end; r.t += r.step) stage_tile<R, NF, WZ, RHS, READ_TN, OUT2, SH>(a, a.tiles[r.t], sh);
 }
 
 // ===========================================================================
@@ -797,14 +914,6 @@ __device__ __forceinline__ void wait_lgkm() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0xC07F);
 }
-// Keeps later LDS reads below a just-issued copy (compiler barrier only).
-__device__ __forceinline__ void mem_order() { asm volatile("" ::: "memory"); }
-
-template <typename R>
-__device__ __forceinline__ R lds_at(const R* slot, uint32_t byte_off) {
-  return *reinterpret_cast<const R*>(reinterpret_cast<const char*>(slot) + byte_off);
-}
-
 // Column-walk form of lat_nb.  The layer's stage input and velocity of all
 // 64 columns of the cell are already in the LDS slot `cur`, so a neighbour
 // column of the same cell (most lateral faces of a locality-ordered mesh) is
@@ -1097,30 +1206,38 @@ hipError_t resident_per_cu(Kern kern, int threads, size_t lds, std::atomic<int>*
   return hipSuccess;
 }
 
-template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2>
-hipError_t launch_mode(const StageArgs& a, hipStream_t s) {
-  const bool walk = a.tile_layers >= kWalkMinLayers;
-  const int threads = walk ? kCell : kCell * a.tile_layers;
+// Launches one kernel over the tiles.
+template <typename Kern>
+hipError_t launch_tiles(Kern kern, const StageArgs& a, int threads, size_t lds, std::atomic<int>* cache,
+                        hipStream_t s) {
   int grid = a.n_tiles;
   if (a.persistent) {
-    static std::atomic<int> cache[kTileChoices + 1];
     int ci = kTileChoices;   // the per-bucket walk table
     for (int i = 0; i < kTileChoices; ++i)
       if (kTileLayerOptions[i] == a.tile_layers) ci = i;
     int per_cu = 1;
-    hipError_t e = walk ? resident_per_cu(&walk_kernel<R, NF, WZ, RHS, READ_TN, OUT2>, threads, 0, &cache[ci], &per_cu)
-                        : resident_per_cu(&stage_kernel<R, NF, WZ, RHS, READ_TN, OUT2>, threads, 0, &cache[ci], &per_cu);
+    hipError_t e = resident_per_cu(kern, threads, lds, &cache[ci], &per_cu);
     if (e != hipSuccess) return e;
     grid = (per_cu * a.n_cu) & ~7;
     if (grid < 8) grid = 8;
     const int need = (a.n_tiles + 7) & ~7;
     if (grid > need) grid = need;
   }
-  if (walk)
-    hipLaunchKernelGGL((walk_kernel<R, NF, WZ, RHS, READ_TN, OUT2>), dim3(grid), dim3(threads), 0, s, a);
-  else
-    hipLaunchKernelGGL((stage_kernel<R, NF, WZ, RHS, READ_TN, OUT2>), dim3(grid), dim3(threads), 0, s, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, s, a);
   return hipGetLastError();
+}
+
+template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2>
+hipError_t launch_mode(const StageArgs& a, hipStream_t s) {
+  static std::atomic<int> walk_cache[kTileChoices + 1], lds_cache[kTileChoices + 1], cache[kTileChoices + 1];
+  if (a.tile_layers >= kWalkMinLayers)
+    return launch_tiles(&walk_kernel<R, NF, WZ, RHS, READ_TN, OUT2>, a, kCell, 0, walk_cache, s);
+  const int threads = kCell * a.tile_layers;
+  // more than one wavefront per SIMD (4 per CU): neighbours in the cell through LDS
+  if ((int64_t)a.n_tiles * a.tile_layers > 4 * (int64_t)a.n_cu)
+    return launch_tiles(&stage_kernel<R, NF, WZ, RHS, READ_TN, OUT2, true>, a, threads,
+                        (size_t)threads * kStageRows<NF> * sizeof(R), lds_cache, s);
+  return launch_tiles(&stage_kernel<R, NF, WZ, RHS, READ_TN, OUT2, false>, a, threads, 0, cache, s);
 }
 
 template <typename R, int NF>
