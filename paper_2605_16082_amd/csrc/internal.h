@@ -10,6 +10,8 @@ namespace sdg {
 
 constexpr int kCell = 64;           // columns per cell = wavefront width
 constexpr int kMaxFields = 4;
+constexpr int kColumnWaves = 8;     // wavefronts that share a cell's layers in the per-column sums
+static_assert(kColumnWaves >= kMaxFields, "wave f adds field f");
 
 // Per-column geometry rows in DevMesh::geo ([kGeoRows][n_col_slots]).
 enum GeoRow : int {
