@@ -768,7 +768,6 @@ sdg_status enqueue_stage(sdg_ctx* ctx, int stage, const void* Tn, const void* Ts
 SolveArgs solve_args(sdg_ctx* ctx, const void* Tstar, void* Tout, double dt) {
   SolveArgs a{};
   a.m = ctx->dm;
-  a.keep_p = !ctx->plan.col_tiles.empty();
   a.n_fields = ctx->plan.F;
   a.Tstar = Tstar;
   a.Tout = Tout;
@@ -783,8 +782,18 @@ SolveArgs solve_args(sdg_ctx* ctx, const void* Tstar, void* Tout, double dt) {
 // kappa, the parameters or the mesh change.
 sdg_status ensure_factors(sdg_ctx* ctx, double dt, hipStream_t strm) {
   if (ctx->efac_valid && ctx->efac_dt == dt) return SDG_OK;
-  hipError_t e = launch_vsolve(solve_args(ctx, nullptr, nullptr, dt), ctx->plan.fp32, ctx->plan.prec == SDG_FP32,
-                               true, strm);
+  hipError_t e;
+  if (ctx->plan.col_tiles.empty()) {
+    e = launch_vsolve(solve_args(ctx, nullptr, nullptr, dt), ctx->plan.fp32, ctx->plan.prec == SDG_FP32, true, strm);
+  } else {
+    ColFactorArgs a{};
+    a.m = ctx->dm;
+    a.kappa = ctx->kappa;
+    a.fac = ctx->scratch;
+    a.dt = dt;
+    a.eta = ctx->eta;
+    e = launch_column_factor(a, ctx->plan.prec == SDG_FP32, strm);
+  }
   if (e != hipSuccess) return hip_fail(e, "column factor launch");
   ctx->efac_valid = true;
   ctx->efac_dt = dt;

@@ -592,6 +592,111 @@ __global__ __launch_bounds__(BT, MW) void column_solve_kernel(ColSolveArgs a) {
   }
 }
 
+// The kept P_l = B_l D'_{l-1}^-1 [:, bottom] of all layers, one lane per column and one
+// wavefront per cell of 64 columns: the recurrence is serial, and bound by the chain
+// of its some 450 operations a layer at one wavefront per SIMD or less.  The pivots
+// are inverted by 3x3 blocks as in the solve above and only the blocks that P needs
+// are formed; against a sweep with the LU of the 6x6 pivots (vsolve.hip's), double,
+// 49,928 x 20 columns 62 -> 43 us, 4,418 x 13 24.7 -> 14.5, 199,712 x 30 211 -> 139;
+// float, 60 ragged layers, 93 -> 92.
+template <typename C>
+struct FactorLayer {
+  C dz[3], h;
+};
+
+template <typename C>
+__global__ __launch_bounds__(64) void column_factor_kernel(ColFactorArgs a) {
+  const DevMesh& m = a.m;
+  const int cell = m.cell_order[blockIdx.x];   // deepest cells first
+  const int lane = threadIdx.x;
+  const int N = m.nlay[cell * kCell + lane];
+  if (N == 0) return;
+  const size_t SL = (size_t)m.n_slots, LS = (size_t)m.n_lslots;
+  const size_t p0 = (size_t)m.cell_base[cell] + lane, lt0 = (size_t)m.cell_lbase[cell] + lane;
+  CPair<C>* __restrict__ Pk = reinterpret_cast<CPair<C>*>(a.fac);
+  const C dt = (C)a.dt;
+  const C pen = dt * (C)a.eta * (C)(0.5 / 24.0);
+  auto load = [&](int l, FactorLayer<C>& g) {
+    const size_t lt = lt0 + (size_t)(l < N ? l : N - 1) * kCell;
+#pragma unroll
+    for (int v = 0; v < 3; ++v) g.dz[v] = (C)(m.zl[v * LS + lt] - m.zl[v * LS + lt + kCell]);
+  };
+  auto mean = [](FactorLayer<C>& g) { g.h = (g.dz[0] + g.dz[1] + g.dz[2]) * (C)(1.0 / 3.0); };
+  FactorLayer<C> g0, g1, g2;       // layers l, l + 1, l + 2
+  load(0, g0);
+  load(1, g1);
+  mean(g0);
+  M3<C> P = {};
+  C tu = (C)0;
+  // the heights and kappa are read two layers ahead
+  auto kap = [&](int l) { return (C)a.kappa[l < N ? l : N - 1]; };
+  C kc = kap(0), kn = kap(1);
+  for (int l = 0; l + 1 < N; ++l) {
+    load(l + 2, g2);
+    const C kn2 = kap(l + 2);
+    mean(g1);
+    const C td = pen * (kc + kn) * recip(g0.h < g1.h ? g0.h : g1.h);
+    // Q = dt kappa/2 sum_q w lambda lambda / D(q)
+    C Q[6], mz[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) Q[i] = (C)0;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const C inv = (C)kTw[q] * recip((C)kL0[q] * g0.dz[0] + (C)kL1[q] * g0.dz[1] + (C)kL2[q] * g0.dz[2]);
+      Q[0] += (C)(kL0[q] * kL0[q]) * inv;
+      Q[1] += (C)(kL1[q] * kL1[q]) * inv;
+      Q[2] += (C)(kL2[q] * kL2[q]) * inv;
+      Q[3] += (C)(kL0[q] * kL1[q]) * inv;
+      Q[4] += (C)(kL0[q] * kL2[q]) * inv;
+      Q[5] += (C)(kL1[q] * kL2[q]) * inv;
+    }
+    const C sq = (C)0.5 * dt * kc;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) Q[i] *= sq;
+    {
+      const C s = (C)(1.0 / 360.0);
+      const C* dz = g0.dz;
+      mz[0] = s * ((C)3 * dz[0] + dz[1] + dz[2]);
+      mz[1] = s * (dz[0] + (C)3 * dz[1] + dz[2]);
+      mz[2] = s * (dz[0] + dz[1] + (C)3 * dz[2]);
+      mz[3] = s * (dz[0] + dz[1] + (C)0.5 * dz[2]);
+      mz[4] = s * (dz[0] + dz[2] + (C)0.5 * dz[1]);
+      mz[5] = s * (dz[1] + dz[2] + (C)0.5 * dz[0]);
+    }
+    // D'_l = [tt tb; bt bb] (a layer below exists); its inverse's right blocks
+    const C fu = l > 0 ? (C)1 : (C)2;
+    M3<C> tt, tb, bt, bb;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const C ps = (C)1 + (P.m[i][0] + P.m[i][1] + P.m[i][2]);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const C mm = mz[sx(i, j)], q = Q[sx(i, j)];
+        const C pq = P.m[i][0] * Q[sx(0, j)] + P.m[i][1] * Q[sx(1, j)] + P.m[i][2] * Q[sx(2, j)];
+        const C e = i == j ? (C)1 : (C)0;
+        tt.m[i][j] = (C)2 * mm + fu * q - pq + tu * (ps + P.m[i][j] + e);
+        tb.m[i][j] = mm - fu * q + pq;
+        bt.m[i][j] = mm - q;
+        bb.m[i][j] = (C)2 * mm + q + td * ((C)1 + e);
+      }
+    }
+    const M3<C> x1 = mul3(inv3(tt), tb);
+    const M3<C> BB = inv3(sub_mul3(bb, bt, x1));
+    const M3<C> TB = neg3(mul3(x1, BB));
+    P = couple3(Q, BB, TB, td, BB);
+    const size_t p = p0 + (size_t)(l + 1) * kCell;
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+      Pk[(size_t)k * SL + p] =
+          CPair<C>{P.m[(2 * k) / 3][(2 * k) % 3], k < 4 ? P.m[(2 * k + 1) / 3][(2 * k + 1) % 3] : (C)0};
+    tu = td;
+    kc = kn;
+    kn = kn2;
+    g0 = g1;
+    g1 = g2;
+  }
+}
+
 template <typename S, typename C, int NF, bool TR, int BT>
 hipError_t launch_block(const ColSolveArgs& a, hipStream_t s) {
   // three wavefronts per SIMD (168 registers): at two the solve of 2,454,178 prisms
@@ -624,6 +729,13 @@ hipError_t launch_nf(const ColSolveArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+hipError_t launch_column_factor(const ColFactorArgs& a, bool fp32_solve, hipStream_t s) {
+  if (a.m.n_cells == 0) return hipSuccess;
+  if (fp32_solve) hipLaunchKernelGGL(column_factor_kernel<float>, dim3(a.m.n_cells), dim3(kCell), 0, s, a);
+  else hipLaunchKernelGGL(column_factor_kernel<double>, dim3(a.m.n_cells), dim3(kCell), 0, s, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_column_solve(const ColSolveArgs& a, bool fp32_state, bool fp32_solve, bool transposed,
                                hipStream_t s) {

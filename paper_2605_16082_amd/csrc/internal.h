@@ -135,9 +135,15 @@ struct ColSolveArgs {
   double dt, eta;
 };
 
+struct ColFactorArgs {
+  DevMesh m;
+  const double* kappa;   // [max_layers]
+  void* fac;             // the P_l, as ColSolveArgs::fac
+  double dt, eta;
+};
+
 struct SolveArgs {
   DevMesh m;
-  int32_t keep_p;        // factor sweep: keep P_l for the layer-parallel solve instead of E_l
   int32_t n_fields;
   const void* Tstar;
   void* Tout;
@@ -174,10 +180,11 @@ hipError_t launch_geometry(const DevMesh& m, double* geo, float* geo32, hipStrea
 hipError_t launch_z32(const DevMesh& m, float* zl32, hipStream_t s);
 hipError_t launch_stage(const StageArgs& a, bool fp32, bool w_zero, bool rhs_only,
                         bool read_tn, hipStream_t s);
-// factor = true: compute and keep the factors for (kappa, dt, eta) in a.scratch
-// (the fields are not read): E_l, or with a.keep_p the P_l of the layer-parallel
-// solve; false: serial solve with kept E_l.
+// factor = true: compute and keep the factors E_l for (kappa, dt, eta) in a.scratch
+// (the fields are not read); false: serial solve with kept E_l.
 hipError_t launch_vsolve(const SolveArgs& a, bool fp32_state, bool fp32_solve, bool factor, hipStream_t s);
+// The P_l of the layer-parallel solve for (kappa, dt, eta).
+hipError_t launch_column_factor(const ColFactorArgs& a, bool fp32_solve, hipStream_t s);
 // The layer-parallel solve (transposed: the adjoint's, FP64 only) with kept P_l.
 hipError_t launch_column_solve(const ColSolveArgs& a, bool fp32_state, bool fp32_solve, bool transposed,
                                hipStream_t s);

@@ -27,8 +27,7 @@
 // recomputes C_l from the levels.
 //
 // These serial sweeps serve meshes with a column deeper than 64 layers; the
-// others take the layer-parallel solve of column_solve.hip, for which the factor
-// sweep here keeps P_l = B_l E_{l-1} instead of E_l (keep_p).
+// others take the layer-parallel solve of column_solve.hip.
 //
 // E_l depends only on the mesh, kappa, dt and the penalty, not on the
 // fields, so it is computed once for a given (kappa, dt, eta) by a sweep
@@ -123,7 +122,7 @@ __device__ __forceinline__ C penalty(C eta, C ka, C kb, C ha, C hb) {
   return eta * (C)0.5 * (ka + kb) / (ha < hb ? ha : hb);
 }
 
-// NF = 0: the factor sweep (store E_l or P_l only, no back substitution);
+// NF = 0: the factor sweep (store E_l only, no back substitution);
 // NF > 0: the solve (store y_l only, back substitution with the kept E_l).
 template <typename S, typename C, int NF>
 __global__ __launch_bounds__(64) void vsolve_kernel(SolveArgs a) {
@@ -243,8 +242,8 @@ __global__ __launch_bounds__(64) void vsolve_kernel(SolveArgs a) {
     }
 
     // Schur complement with the layer above
-    C P[3][3];
     if (l > 0) {
+      C P[3][3];
       // B_l = dt [-kp Kvp/2 | kp Kvp/2 - sig_u S]  (3 x 6)
       C Bm[3][6];
 #pragma unroll
@@ -355,14 +354,7 @@ __global__ __launch_bounds__(64) void vsolve_kernel(SolveArgs a) {
     for (int i = 0; i < 6; ++i)
 #pragma unroll
       for (int q = 0; q < 3; ++q) Ep[i][q] = Ec[i][q];
-    if (NF == 0 && a.keep_p) {
-      if (l > 0) {
-#pragma unroll
-        for (int k = 0; k < 5; ++k)
-          Psc[(size_t)k * SL + p] =
-              CPair<C>{P[(2 * k) / 3][(2 * k) % 3], k < 4 ? P[(2 * k + 1) / 3][(2 * k + 1) % 3] : (C)0.0};
-      }
-    } else if (NF == 0) {
+    if (NF == 0) {
 #pragma unroll
       for (int k = 0; k < 9; ++k)
         Psc[(size_t)k * SL + p] = CPair<C>{Ec[(2 * k) / 3][(2 * k) % 3], Ec[(2 * k + 1) / 3][(2 * k + 1) % 3]};
