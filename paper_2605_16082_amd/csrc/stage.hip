@@ -31,6 +31,8 @@
 //    control flow: lanes past their column's depth compute on in-bounds
 //    padding slots and skip the store, and faces without a neighbour address
 //    the prism's own nodes and select the exterior value.
+//    On launches of more than one wavefront per SIMD each wavefront reads its
+//    neighbours in the cell from its layer's rows in LDS.
 //
 //  * walk_kernel: one wavefront walks down a segment of a cell's layers.
 //    The next layer's stage input, velocity, bottom level heights (and Tn,
@@ -89,27 +91,19 @@ template <typename T>
 __device__ __forceinline__ void stb(T* __restrict__ row, uint32_t byte_off, T v) {
   *reinterpret_cast<T*>(reinterpret_cast<char*>(row) + byte_off) = v;
 }
-// Row r of a [..][6][S] nodal array at byte offset off.  In double the
-// address is the base of the row's 6-row block plus a 32-bit offset
-// (r mod 6) S + off: one uniform base per block instead of one per row, so
-// the FP64 column walk keeps far fewer 64-bit row addresses in scalar
-// registers, which it otherwise spills to vector lanes (stages 2% faster).
-// In float the per-row form stays: the block form's offsets take the few
-// vector registers that keep the float walk at two wavefronts per SIMD.
-// A 6-row block is below 4 GiB (checked at mesh upload).
+// Row r of a [..][6][S] nodal array at byte offset off: the address is the base of
+// the row's 6-row block plus a 32-bit offset (r mod 6) S + off, so there is one
+// uniform base per block instead of one per row; the kernels keep far fewer 64-bit
+// row addresses in scalar registers, which they otherwise spill to vector lanes
+// (double stages 2% faster; the float walk of 4 fields executes 5% fewer
+// instructions).  A 6-row block is below 4 GiB (checked at mesh upload).
 template <typename T>
 __device__ __forceinline__ T ldr(const T* __restrict__ arr, size_t S, int r, uint32_t off) {
-  if constexpr (sizeof(T) == 8)
-    return ldb(arr + (size_t)(r / 6 * 6) * S, (uint32_t)(r % 6) * (uint32_t)(S * sizeof(T)) + off);
-  else
-    return ldb(arr + (size_t)r * S, off);
+  return ldb(arr + (size_t)(r / 6 * 6) * S, (uint32_t)(r % 6) * (uint32_t)(S * sizeof(T)) + off);
 }
 template <typename T>
 __device__ __forceinline__ void str(T* __restrict__ arr, size_t S, int r, uint32_t off, T v) {
-  if constexpr (sizeof(T) == 8)
-    stb(arr + (size_t)(r / 6 * 6) * S, (uint32_t)(r % 6) * (uint32_t)(S * sizeof(T)) + off, v);
-  else
-    stb(arr + (size_t)r * S, off, v);
+  stb(arr + (size_t)(r / 6 * 6) * S, (uint32_t)(r % 6) * (uint32_t)(S * sizeof(T)) + off, v);
 }
 
 template <typename R>
@@ -221,7 +215,7 @@ __device__ __forceinline__ void volume_term(const ColGeo<R>& g, const R zt[3], c
   }
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    R sx[2], se[2], sz[3] = {R(0), R(0), R(0)};
+    R sx[2], se[2], sz[3];
     R T[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) T[i] = own(f, i);
@@ -233,9 +227,16 @@ __device__ __forceinline__ void volume_term(const ColGeo<R>& g, const R zt[3], c
       for (int n = 0; n < 3; ++n) ta[n] = tk * T[n] + bk * T[n + 3];
       sx[k] = ta[0] * Px[k][0] + ta[1] * Px[k][1] + ta[2] * Px[k][2];
       se[k] = ta[0] * Pe[k][0] + ta[1] * Pe[k][1] + ta[2] * Pe[k][2];
-      sz[0] += G[k][0] * ta[0] + G[k][3] * ta[1] + G[k][4] * ta[2];
-      sz[1] += G[k][3] * ta[0] + G[k][1] * ta[1] + G[k][5] * ta[2];
-      sz[2] += G[k][4] * ta[0] + G[k][5] * ta[1] + G[k][2] * ta[2];
+      const R g[3][3] = {{G[k][0], G[k][3], G[k][4]}, {G[k][3], G[k][1], G[k][5]}, {G[k][4], G[k][5], G[k][2]}};
+#pragma unroll
+      for (int n = 0; n < 3; ++n) {
+        if (k == 0)
+          sz[n] = g[n][0] * ta[0];
+        else
+          sz[n] += g[n][0] * ta[0];
+        sz[n] += g[n][1] * ta[1];
+        sz[n] += g[n][2] * ta[2];
+      }
     }
     // dphi/dxi = dlambda/dxi * (t or b), dphi/dzeta = +-lambda/2
     const R sxt = R(kZt[0]) * sx[0] + R(kZt[1]) * sx[1];
@@ -481,14 +482,26 @@ __device__ __forceinline__ void lat_apply(int e, const LatQ<R>& F, Own own, cons
     for (int f = 0; f < NF; ++f) {
       const R TA = own(f, A), TB = own(f, B), TA3 = own(f, A + 3), TB3 = own(f, B + 3);
       const R* o = to[f];
-      res[f][A] -= Kp[0][0] * TA + Kp[1][0] * TB + Kp[0][1] * TA3 + Kp[1][1] * TB3 +
-                   (Km[0][0] * o[0] + Km[1][0] * o[1] + Km[0][1] * o[2] + Km[1][1] * o[3]);
-      res[f][B] -= Kp[1][0] * TA + Kp[2][0] * TB + Kp[1][1] * TA3 + Kp[2][1] * TB3 +
-                   (Km[1][0] * o[0] + Km[2][0] * o[1] + Km[1][1] * o[2] + Km[2][1] * o[3]);
-      res[f][A + 3] -= Kp[0][1] * TA + Kp[1][1] * TB + Kp[0][2] * TA3 + Kp[1][2] * TB3 +
-                       (Km[0][1] * o[0] + Km[1][1] * o[1] + Km[0][2] * o[2] + Km[1][2] * o[3]);
-      res[f][B + 3] -= Kp[1][1] * TA + Kp[2][1] * TB + Kp[1][2] * TA3 + Kp[2][2] * TB3 +
-                       (Km[1][1] * o[0] + Km[2][1] * o[1] + Km[1][2] * o[2] + Km[2][2] * o[3]);
+      const R Ti[4] = {TA, TB, TA3, TB3};
+      R* r = res[f];
+      // one multiply-add a product (FP32 2 fields 0.71 M prisms 41.1 -> 39.0 us, the walk
+      // of 8 layers with 4 fields 634 -> 623)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const int x = n & 1, y = n >> 1;
+        r[A] -= Kp[x][y] * Ti[n];
+        r[B] -= Kp[1 + x][y] * Ti[n];
+        r[A + 3] -= Kp[x][1 + y] * Ti[n];
+        r[B + 3] -= Kp[1 + x][1 + y] * Ti[n];
+      }
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const int x = n & 1, y = n >> 1;
+        r[A] -= Km[x][y] * o[n];
+        r[B] -= Km[1 + x][y] * o[n];
+        r[A + 3] -= Km[x][1 + y] * o[n];
+        r[B + 3] -= Km[1 + x][1 + y] * o[n];
+      }
     }
   }
 }
@@ -556,9 +569,17 @@ __device__ __forceinline__ void hface_field(const HorF<R>& F, R te, const R Tu[3
     tu[n] = F.has_up ? Tu[n] : te;
     tl[n] = F.has_lo ? Tl[n] : te;
   }
-  g[0] = F.gp[0] * tl[0] + F.gp[3] * tl[1] + F.gp[4] * tl[2] + (F.gm[0] * tu[0] + F.gm[3] * tu[1] + F.gm[4] * tu[2]);
-  g[1] = F.gp[3] * tl[0] + F.gp[1] * tl[1] + F.gp[5] * tl[2] + (F.gm[3] * tu[0] + F.gm[1] * tu[1] + F.gm[5] * tu[2]);
-  g[2] = F.gp[4] * tl[0] + F.gp[5] * tl[1] + F.gp[2] * tl[2] + (F.gm[4] * tu[0] + F.gm[5] * tu[1] + F.gm[2] * tu[2]);
+  const R gp[3][3] = {{F.gp[0], F.gp[3], F.gp[4]}, {F.gp[3], F.gp[1], F.gp[5]}, {F.gp[4], F.gp[5], F.gp[2]}};
+  const R gm[3][3] = {{F.gm[0], F.gm[3], F.gm[4]}, {F.gm[3], F.gm[1], F.gm[5]}, {F.gm[4], F.gm[5], F.gm[2]}};
+#pragma unroll
+  for (int n = 0; n < 3; ++n) {
+    g[n] = gp[n][0] * tl[0];
+    g[n] += gp[n][1] * tl[1];
+    g[n] += gp[n][2] * tl[2];
+    g[n] += gm[n][0] * tu[0];
+    g[n] += gm[n][1] * tu[1];
+    g[n] += gm[n][2] * tu[2];
+  }
 }
 
 // Mz = J_h/120 * m with m_aa = 3 dz_a + dz_b + dz_c, m_ab = dz_a + dz_b + dz_c/2;
