@@ -335,8 +335,9 @@ struct sdg_ctx {
   void* stage_a = nullptr;
   void* stage_b = nullptr;
   double* scratch = nullptr;
-  // the solve scratch holds the block-Thomas factors of (kappa, efac_dt, eta),
-  // tfac those of the transposed system for tfac_dt
+  // the solve scratch holds the column factors of (kappa, efac_dt, eta): P_l for the
+  // layer-parallel solve and its transpose, or E_l for the serial sweeps, whose
+  // transposed system has its own in tfac, for tfac_dt
   bool efac_valid = false;
   double efac_dt = 0.0;
   double* tfac = nullptr;
