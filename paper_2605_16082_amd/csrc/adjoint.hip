@@ -1047,12 +1047,14 @@ __global__ __launch_bounds__(kCell * kColumnWaves) void mdot_column_kernel(DevMe
 
 template <int NF>
 hipError_t launch_adj_stage_nf(const AdjStageArgs& a, bool w_zero, int tile_layers, int n_cu, hipStream_t s) {
-  const dim3 grid(a.n_tiles), block(kCell * tile_layers);
+  // no wavefronts for layers that no cell has, as in the forward stages
+  const int layers = tile_layers < a.m.max_layers ? tile_layers : a.m.max_layers;
+  const dim3 grid(a.n_tiles), block(kCell * layers);
   // more than 16 wavefronts per CU: neighbours in the cell through LDS.  Reverse step
   // (three of these kernels and a solve), without -> with LDS, FP64: 15602 wavefronts 1
   // field 317 -> 288 us, 2 fields 492 -> 437, 4 fields 851 -> 808; 4050 wavefronts 88.6
   // -> 87.4, 121 -> 120, 195 -> 200; 897 wavefronts 37.5 -> 39.7, 48.8 -> 50.2, 66 -> 67.
-  if ((int64_t)a.n_tiles * tile_layers > 16 * (int64_t)n_cu) {
+  if ((int64_t)a.n_tiles * layers > 16 * (int64_t)n_cu) {
     const size_t lds = block.x * kAdjRows<NF> * sizeof(double);
     if (w_zero) hipLaunchKernelGGL((adj_stage_kernel<NF, true, true>), grid, block, lds, s, a);
     else hipLaunchKernelGGL((adj_stage_kernel<NF, false, true>), grid, block, lds, s, a);
