@@ -944,14 +944,16 @@ __global__ __launch_bounds__(256) void kgrad_reduce_kernel(DevMesh m, const doub
 // One thread per prism, four layers of a cell a block: a walk down each column by one
 // thread left the launch at a few wavefronts per CU with one layer's loads in flight
 // (whole call, new result included: 2 fields of 55 k prisms 16.6 -> 11.4 us, float 2
-// fields of 0.71 M 46 -> 22, 4 fields of 2.6 M ragged prisms 419 -> 350).
+// fields of 0.71 M 46 -> 22, 4 fields of 2.6 M ragged prisms 419 -> 350).  Shallower
+// meshes take a block of as many wavefronts as they have layers (180,000 columns of one
+// layer, 4 fields: 13.5 us with four, 13.1 with one).
 constexpr int kMassLayers = 4;
 template <typename R>
 __global__ __launch_bounds__(kCell * kMassLayers) void mass_apply_kernel(DevMesh m, const R* X, R* Y, int nf,
                                                                          int inverse) {
   const int cell = blockIdx.x;
   const int lane = threadIdx.x % kCell;
-  const int l = blockIdx.y * kMassLayers + threadIdx.x / kCell;
+  const int l = (blockIdx.y * blockDim.x + threadIdx.x) / kCell;
   const int c = cell * kCell + lane;
   if (l >= m.nlay[c]) return;
   const size_t SL = (size_t)m.n_slots;
@@ -992,23 +994,23 @@ __global__ __launch_bounds__(kCell * kMassLayers) void mass_apply_kernel(DevMesh
   }
 }
 
-// Per column and field X^T M Y.  A block of kColumnWaves wavefronts takes a cell; wave
-// k adds the layers k, k + kColumnWaves, ... in this order, and the waves' sums are
-// added in theirs, so the result is the same on every call (whole call, one thread per
-// column -> now: 1 field of 1.0 M prisms 100 -> 47 us, 4 fields of 6.0 M 491 -> 331).
+// Per column and field X^T M Y.  A block of column_waves() wavefronts takes a cell; wave
+// k adds the layers k, k + waves, ... in this order, and the waves' sums are added in
+// theirs, so the result is the same on every call (whole call, one thread per column ->
+// now: 1 field of 1.0 M prisms 100 -> 47 us, 4 fields of 6.0 M 491 -> 331).
 template <typename R>
 __global__ __launch_bounds__(kCell * kColumnWaves) void mdot_column_kernel(DevMesh m, const R* X, const R* Y, int nf,
                                                                            double* out) {
   __shared__ double part[kColumnWaves][kMaxFields][kCell];
   const int cell = blockIdx.x;
-  const int lane = threadIdx.x % kCell, wave = threadIdx.x / kCell;
+  const int lane = threadIdx.x % kCell, wave = threadIdx.x / kCell, waves = blockDim.x / kCell;
   const int c = cell * kCell + lane;
   const int N = m.nlay[c];
   const int CS = m.n_col_slots;
   const size_t SL = (size_t)m.n_slots;
   double acc[kMaxFields] = {0.0, 0.0, 0.0, 0.0};
   const double Jh = m.geo[G_JH * CS + c];
-  for (int l = wave; l < N; l += kColumnWaves) {
+  for (int l = wave; l < N; l += waves) {
     const size_t p = (size_t)m.cell_base[cell] + (size_t)l * kCell + lane;
     LayerGeo g;
     load_layer(m, (size_t)m.cell_lbase[cell] + (size_t)l * kCell + lane, g);
@@ -1040,7 +1042,7 @@ __global__ __launch_bounds__(kCell * kColumnWaves) void mdot_column_kernel(DevMe
   if (wave < nf) {
     double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < kColumnWaves; ++k) s += part[k][wave][lane];
+    for (int k = 0; k < kColumnWaves; ++k) s += k < waves ? part[k][wave][lane] : 0.0;
     out[(size_t)wave * CS + c] = s;
   }
 }
@@ -1148,7 +1150,8 @@ hipError_t launch_kappa_gradient(const DevMesh& m, const WgTile* tiles2, int n_t
 
 hipError_t launch_mass_apply(const DevMesh& m, const void* X, void* Y, int n_fields, bool fp32, bool inverse,
                              hipStream_t s) {
-  const dim3 grid(m.n_cells, (m.max_layers + kMassLayers - 1) / kMassLayers), block(kCell * kMassLayers);
+  const int rows = m.max_layers < kMassLayers ? m.max_layers : kMassLayers;
+  const dim3 grid(m.n_cells, (m.max_layers + rows - 1) / rows), block(kCell * rows);
   if (fp32)
     hipLaunchKernelGGL(mass_apply_kernel<float>, grid, block, 0, s, m,
                        static_cast<const float*>(X), static_cast<float*>(Y), n_fields, (int)inverse);
@@ -1161,10 +1164,10 @@ hipError_t launch_mass_apply(const DevMesh& m, const void* X, void* Y, int n_fie
 hipError_t launch_mdot_columns(const DevMesh& m, const void* X, const void* Y, int n_fields, bool fp32,
                                double* col_out, hipStream_t s) {
   if (fp32)
-    hipLaunchKernelGGL(mdot_column_kernel<float>, dim3(m.n_cells), dim3(kCell * kColumnWaves), 0, s, m,
+    hipLaunchKernelGGL(mdot_column_kernel<float>, dim3(m.n_cells), dim3(kCell * column_waves(m, n_fields)), 0, s, m,
                        static_cast<const float*>(X), static_cast<const float*>(Y), n_fields, col_out);
   else
-    hipLaunchKernelGGL(mdot_column_kernel<double>, dim3(m.n_cells), dim3(kCell * kColumnWaves), 0, s, m,
+    hipLaunchKernelGGL(mdot_column_kernel<double>, dim3(m.n_cells), dim3(kCell * column_waves(m, n_fields)), 0, s, m,
                        static_cast<const double*>(X), static_cast<const double*>(Y), n_fields, col_out);
   return hipGetLastError();
 }

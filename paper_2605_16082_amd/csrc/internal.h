@@ -10,7 +10,7 @@ namespace sdg {
 
 constexpr int kCell = 64;           // columns per cell = wavefront width
 constexpr int kMaxFields = 4;
-constexpr int kColumnWaves = 8;     // wavefronts that share a cell's layers in the per-column sums
+constexpr int kColumnWaves = 8;     // wavefronts that share a cell's layers in the per-column sums, at most
 static_assert(kColumnWaves >= kMaxFields, "wave f adds field f");
 
 // Per-column geometry rows in DevMesh::geo ([kGeoRows][n_col_slots]).
@@ -218,6 +218,12 @@ hipError_t launch_mass_apply(const DevMesh& m, const void* X, void* Y, int n_fie
                              hipStream_t s);
 hipError_t launch_mdot_columns(const DevMesh& m, const void* X, const void* Y, int n_fields, bool fp32,
                                double* col_out, hipStream_t s);
+
+// Wavefronts of the per-column sums: no more than the mesh has layers, but one a field.
+inline int column_waves(const DevMesh& m, int n_fields) {
+  const int w = m.max_layers < kColumnWaves ? m.max_layers : kColumnWaves;
+  return w < n_fields ? n_fields : w;
+}
 
 // Workgroup index -> tile index so that each of the 8 XCDs (which receive
 // workgroups round-robin) processes one contiguous range of tiles, keeping

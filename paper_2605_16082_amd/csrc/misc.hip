@@ -49,23 +49,24 @@ __global__ __launch_bounds__(256) void to_float_kernel(const double* src, float*
 }
 
 // Per column and field: sum over layers of 1^T M T.  1^T M = [w w] with
-// w_b = sum_a Mz_ab = J_h (2 dz_b + dz_others) / 48.  A block of kColumnWaves
-// wavefronts takes a cell; wave k adds the layers k, k + kColumnWaves, ... in this
-// order, and the waves' sums are added in theirs, so the result is the same on every
-// call (one thread per column had one layer's loads in flight;
-// the mass call of 1 field of 1.0 M prisms 93 -> 43 us, 4 fields of 6.0 M 434 -> 283).
+// w_b = sum_a Mz_ab = J_h (2 dz_b + dz_others) / 48.  A block of column_waves()
+// wavefronts takes a cell; wave k adds the layers k, k + waves, ... in this order, and
+// the waves' sums are added in theirs, so the result is the same on every call (one
+// thread per column had one layer's loads in flight;
+// the mass call of 1 field of 1.0 M prisms 93 -> 43 us, 4 fields of 6.0 M 434 -> 283;
+// eight wavefronts whatever the depth cost 4 fields of 2,813 cells of one layer 56 for 54).
 template <typename R>
 __global__ __launch_bounds__(kCell * kColumnWaves) void column_mass_kernel(DevMesh m, const R* T, int nf, double* out) {
   __shared__ double part[kColumnWaves][kMaxFields][kCell];
   const int cell = blockIdx.x;
-  const int lane = threadIdx.x % kCell, wave = threadIdx.x / kCell;
+  const int lane = threadIdx.x % kCell, wave = threadIdx.x / kCell, waves = blockDim.x / kCell;
   const int c = cell * kCell + lane;
   const int N = m.nlay[c];
   const int CS = m.n_col_slots;
   const size_t SL = (size_t)m.n_slots, LS = (size_t)m.n_lslots;
   double acc[kMaxFields] = {0.0, 0.0, 0.0, 0.0};
   const double Jh = m.geo[G_JH * CS + c];
-  for (int l = wave; l < N; l += kColumnWaves) {
+  for (int l = wave; l < N; l += waves) {
     const size_t p = (size_t)m.cell_base[cell] + (size_t)l * kCell + lane;
     const size_t lt = (size_t)m.cell_lbase[cell] + (size_t)l * kCell + lane;
     double dz[3];
@@ -88,7 +89,7 @@ __global__ __launch_bounds__(kCell * kColumnWaves) void column_mass_kernel(DevMe
   if (wave < nf) {
     double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < kColumnWaves; ++k) s += part[k][wave][lane];
+    for (int k = 0; k < kColumnWaves; ++k) s += k < waves ? part[k][wave][lane] : 0.0;
     out[(size_t)wave * CS + c] = s;
   }
 }
@@ -115,11 +116,15 @@ __global__ __launch_bounds__(kMemberThreads) void member_sum_kernel(const double
   }
   red[threadIdx.x] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
   __syncthreads();
-  for (int w = kMemberThreads / 2; w > 0; w >>= 1) {
+  for (int w = kMemberThreads / 2; w >= kCell; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+  if (threadIdx.x >= kCell) return;
+  double sum = red[threadIdx.x];   // the tree's last levels, in one wavefront
+#pragma unroll
+  for (int w = kCell / 2; w > 0; w >>= 1) sum += __shfl_down(sum, w);
+  if (threadIdx.x == 0) out[blockIdx.x] = sum;
 }
 
 // Live slots only: padding slots of caller buffers are never inspected.
@@ -157,10 +162,10 @@ hipError_t launch_z32(const DevMesh& m, float* zl32, hipStream_t s) {
 hipError_t launch_column_mass(const DevMesh& m, const void* T, int n_fields, bool fp32,
                               double* col_mass, hipStream_t s) {
   if (fp32)
-    hipLaunchKernelGGL(column_mass_kernel<float>, dim3(m.n_cells), dim3(kCell * kColumnWaves), 0, s, m,
+    hipLaunchKernelGGL(column_mass_kernel<float>, dim3(m.n_cells), dim3(kCell * column_waves(m, n_fields)), 0, s, m,
                        static_cast<const float*>(T), n_fields, col_mass);
   else
-    hipLaunchKernelGGL(column_mass_kernel<double>, dim3(m.n_cells), dim3(kCell * kColumnWaves), 0, s, m,
+    hipLaunchKernelGGL(column_mass_kernel<double>, dim3(m.n_cells), dim3(kCell * column_waves(m, n_fields)), 0, s, m,
                        static_cast<const double*>(T), n_fields, col_mass);
   return hipGetLastError();
 }
