@@ -265,9 +265,11 @@ __device__ __forceinline__ void wait_copies() {
   asm volatile("" ::: "memory");
 }
 
-// A block's prisms, thread = (layer, column) with the columns fastest.
-template <typename S, typename C, int NF, bool TR, int BT, int MW>
-__global__ __launch_bounds__(BT, MW) void column_solve_kernel(ColSolveArgs a) {
+// A block's prisms, thread = (layer, column) with the columns fastest.  At least MW and
+// at most MX wavefronts a SIMD.
+template <typename S, typename C, int NF, bool TR, int BT, int MW, int MX>
+__global__ __attribute__((amdgpu_flat_work_group_size(1, BT), amdgpu_waves_per_eu(MW, MX))) void
+column_solve_kernel(ColSolveArgs a) {
   extern __shared__ __align__(16) char smem[];
   using Lds = ColLds<S, C, NF, BT>;
   constexpr int kRow = Lds::kRow;
@@ -496,6 +498,19 @@ __global__ __launch_bounds__(BT, MW) void column_solve_kernel(ColSolveArgs a) {
         for (int i = 0; i < 6; ++i) y[f][i] = yst[(f * 6 + i) * 64];
     }
   }
+  auto store = [&](int f) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+      *reinterpret_cast<S*>(reinterpret_cast<char*>(Tout + (size_t)(f * 6 + i) * SL) + po) = (S)y[f][i];
+  };
+  // a block of one wavefront holds columns of one layer: x = y (without the rest, FP64,
+  // 512 such columns of 1 field 4.8 -> 3.9 us, 51,200 of 4 fields 7.8 -> 7.0)
+  if constexpr (BT == kCell) {
+    if (live)
+#pragma unroll
+      for (int f = 0; f < NF; ++f) store(f);
+    return;
+  }
   phase();
   __syncthreads();   // the chain arrays take the staging space
   // prisms that feed no other get K = 0 and c = 0 (below a column's seabed for
@@ -585,9 +600,7 @@ __global__ __launch_bounds__(BT, MW) void column_solve_kernel(ColSolveArgs a) {
           }
         }
       }
-#pragma unroll
-      for (int i = 0; i < 6; ++i)
-        *reinterpret_cast<S*>(reinterpret_cast<char*>(Tout + (size_t)(f * 6 + i) * SL) + po) = (S)y[f][i];
+      store(f);
     }
   }
 }
@@ -704,7 +717,17 @@ hipError_t launch_block(const ColSolveArgs& a, hipStream_t s) {
   // one field: 93 us against 64).  The float solve fits five.
   constexpr int MW = 3;
   constexpr size_t lds = ColLds<S, C, NF, BT>::kBytes;
-  hipLaunchKernelGGL((column_solve_kernel<S, C, NF, TR, BT, MW>), dim3(a.n_tiles), dim3(BT), lds, s, a);
+  // Columns of two layers, and no more wavefronts than SIMDs: one wavefront a SIMD, as
+  // the dispatcher would put a CU's second block of two on the SIMDs of its first
+  // (22,050 x 2 columns, FP64 4 fields 13.2 -> 10.7 us, 1 field 7.5 -> 6.3).  Blocks of four
+  // wavefronts spread by themselves.
+  if constexpr (BT == 2 * kCell && !TR) {
+    if (a.n_tiles * (BT / kCell) <= 4 * a.n_cu) {
+      hipLaunchKernelGGL((column_solve_kernel<S, C, NF, TR, BT, 1, 1>), dim3(a.n_tiles), dim3(BT), lds, s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((column_solve_kernel<S, C, NF, TR, BT, MW, 8>), dim3(a.n_tiles), dim3(BT), lds, s, a);
   return hipGetLastError();
 }
 

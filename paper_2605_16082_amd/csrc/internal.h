@@ -126,6 +126,7 @@ struct ColSolveArgs {
   const ColTile* tiles;
   int32_t n_tiles;
   int32_t max_np;        // largest depth << log2cols of the table
+  int32_t n_cu;          // compute units of the device
   int32_t n_fields;
   int32_t aligned;       // Tstar is 16-byte aligned (its rows then are)
   const void* Tstar;     // may be the same array as Tout

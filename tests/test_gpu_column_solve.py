@@ -27,7 +27,7 @@ IDS = [f"{w.name}-{w.n_cols}x{int(w.nlayers.max())}-{w.n_fields}" for w in MESHE
 
 
 # double: the bar of every other double result; float state: twice the output's own
-# rounding (2^-24).  The all-float form is compared in test_gpu_parity.py.
+# rounding (2^-24).  The all-float form has a bound of its own below.
 @pytest.mark.parametrize("precision,tol", [(P.SDG_FP64, 1e-12), (P.SDG_FP32_STATE_FP64_SOLVE, 1.2e-7)])
 @pytest.mark.parametrize("w", MESHES, ids=IDS)
 def test_solve_matches_oracle(w, precision, tol):
@@ -40,6 +40,40 @@ def test_solve_matches_oracle(w, precision, tol):
     s.sync()
     scale = np.abs(ref).max(axis=(1, 2))
     assert (np.abs(s.gather(out) - ref).max(axis=(1, 2)) <= tol * scale).all()
+    assert np.array_equal(s.gather(state), s.gather(out))
+
+
+def float_bound(w, m, T):
+    """Bound of each value's error in the all-float solve, (F, 6, P): to first order
+    |S^-1| (|dS| |x| + |db|) with S the column's system and b = M T*.  S and b are sums
+    of at most 20 float products each, and the elimination of a layer (two 3x3
+    inverses, their products with the couplings and with y) rounds at most 44 more times
+    at the size of the system's own terms: 64 * 2^-24 of |S| |x| + |M| |T*| in all."""
+    bound = np.empty_like(T)
+    for c in range(m.C):
+        S, Mc = O.prism_dg.column_system(m, w.kappa, w.dt, c, w.penalty)
+        ps = m.off[c] + np.arange(int(m.nl[c]))
+        t = T[:, :, ps].transpose(2, 1, 0).reshape(len(S), -1)
+        inv = np.linalg.inv(S)
+        terms = np.abs(S) @ np.abs(inv @ (Mc @ t)) + np.abs(Mc) @ np.abs(t)
+        b = 64 * 2.0 ** -24 * np.abs(inv) @ terms
+        bound[:, :, ps] = b.reshape(len(ps), 6, -1).transpose(2, 1, 0)
+    return bound
+
+
+FLOAT_MESHES = MESHES + [_sigma(4, d, f) for d, f in [(1, 1), (1, 4), (2, 1), (2, 2), (2, 3), (2, 4), (3, 4)]]
+
+
+@pytest.mark.parametrize("w", FLOAT_MESHES, ids=lambda w: f"{w.name}-{w.n_cols}x{int(w.nlayers.max())}-{w.n_fields}")
+def test_all_float_solve_matches_oracle(w):
+    s, _, _, state = P.from_workload(w, P.SDG_FP32)
+    T = s.gather(state)
+    m = O.PrismMesh(w.vxy, w.tri, w.nbr, w.nlayers, w.zlev)
+    ref = O.implicit_solve(m, w.kappa, w.dt, T, w.penalty)
+    out = s.vertical_implicit_solve(state)
+    s.vertical_implicit_solve(state, state)
+    s.sync()
+    assert (np.abs(s.gather(out) - ref) <= float_bound(w, m, T)).all()
     assert np.array_equal(s.gather(state), s.gather(out))
 
 

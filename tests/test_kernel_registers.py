@@ -37,3 +37,10 @@ def test_small_stage_launches_get_a_simd_for_each_wavefront(tmp_path):
     small = {k: v for k, v in regs.items() if k.endswith("Lb0EEEvNS_9StageArgsE")}   # the last argument: SH
     assert len(small) == 64 and len(regs) == 128
     assert min(small.values()) > 256, min(small.items(), key=lambda kv: kv[1])
+
+
+def test_small_two_layer_solves_get_a_simd_for_each_wavefront(tmp_path):
+    regs = _reserved(tmp_path, "19column_solve_kernel")
+    small = {k: v for k, v in regs.items() if "Li128ELi1ELi1E" in k}     # threads, wavefronts a SIMD
+    assert len(small) == 12                                              # 3 precision forms of 1 to 4 fields
+    assert min(small.values()) > 256, min(small.items(), key=lambda kv: kv[1])
