@@ -66,11 +66,8 @@ struct Plan {
   size_t state_bytes, velocity_bytes;
 };
 
-// Column groups of the layer-parallel solves: per cell the largest power of two
-// of columns whose prisms fit a block of kColSolveMaxPrisms threads (4 columns at 64
-// layers, where a lane's 16-byte copies still hold whole columns; blocks of 512 with
-// twice the columns were 10-15% slower).  Deepest cells first, as the longest.
-void plan_column_blocks(Plan& P) {
+// The blocks of the layer-parallel solves, or none where the serial sweeps are used.
+void plan_column_solves(Plan& P) {
   P.col_tiles.clear();
   P.col_max_np = 0;
   if (P.max_layers > kColSolveMaxLayers) return;
@@ -78,14 +75,8 @@ void plan_column_blocks(Plan& P) {
   // longer than a block's barriers (16,562 columns, 4 fields 9.0 us against 10.3 in
   // blocks, 80,000 columns 14.8 against 16.0; 2 fields 7.4 against 6.7)
   if (P.prec == SDG_FP32 && P.max_layers == 2 && P.F >= 3) return;
-  for (int32_t k : P.cell_order) {
-    const int D = P.cell_depth[k];
-    int g = 6;
-    while ((D << g) > kColSolveMaxPrisms) --g;
-    for (int c0 = 0; c0 < kCell && k * kCell + c0 < P.C; c0 += 1 << g)
-      P.col_tiles.push_back({P.cell_base[k] + c0, P.cell_lbase[k] + c0, k * kCell + c0, (uint16_t)D, (uint16_t)g});
-    P.col_max_np = std::max(P.col_max_np, D << g);
-  }
+  P.col_tiles =
+      plan_column_blocks(kCell, P.C, P.cell_order, P.cell_depth, P.cell_base, P.cell_lbase, &P.col_max_np);
 }
 
 sdg_status plan_mesh(const sdg_mesh_desc* d, Plan& P) {
@@ -202,7 +193,7 @@ sdg_status plan_mesh(const sdg_mesh_desc* d, Plan& P) {
   for (int k = 0; k < P.n_cells; ++k) P.cell_order[k] = k;
   std::stable_sort(P.cell_order.begin(), P.cell_order.end(),
                    [&](int32_t x, int32_t y) { return P.cell_depth[x] > P.cell_depth[y]; });
-  plan_column_blocks(P);
+  plan_column_solves(P);
   P.halo_max = 0;
   for (int k = 0; k < P.n_cells; ++k) {
     P.halo_max = std::max(P.halo_max, P.halo_off[k + 1]);

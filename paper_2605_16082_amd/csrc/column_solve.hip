@@ -26,7 +26,7 @@
 // fields, double 1158 -> 800 us (2.9 GB at 3.6 TB/s; some 70 us less without the
 // two chains, 90 without the stores: a block's loads all come at its start, so
 // memory idles while it computes), float state 1033 -> 606, float 586 -> 480;
-// 68,220 ragged columns to 60 layers, 4 fields 1106 -> 529; 49,928 x 20, 1 field
+// 68,220 ragged columns to 60 layers, 4 fields 1106 -> 452; 49,928 x 20, 1 field
 // 115 -> 64; 1,800 x 10, 1 field 32 -> 7.
 #include "internal.h"
 

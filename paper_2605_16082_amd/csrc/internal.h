@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "column_blocks.h"
+
 namespace sdg {
 
 constexpr int kCell = 64;           // columns per cell = wavefront width
@@ -108,19 +110,7 @@ struct StageArgs {
   double a, b;         // Tout = a Tn + b (Ts + dt L)
 };
 
-// Layer-parallel column solves: a block takes 2^log2cols consecutive columns of a
-// cell over the cell's depth, one thread per prism.
-struct ColTile {
-  int32_t base;       // prism slot of the first column's layer 0
-  int32_t lbase;      // its level slot
-  int32_t col;        // its column slot
-  uint16_t depth;     // layers of the cell
-  uint16_t log2cols;
-};
-constexpr int kColSolveMaxLayers = 64;    // deeper meshes take the serial sweeps
-constexpr int kColSolveMaxPrisms = 256;   // prisms (threads) of a block
-static_assert(kColSolveMaxPrisms / kColSolveMaxLayers >= 4, "16-byte copies need 4 columns a block");
-
+// Layer-parallel column solves (block table: column_blocks.h).
 struct ColSolveArgs {
   DevMesh m;
   const ColTile* tiles;
