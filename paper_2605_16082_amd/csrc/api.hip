@@ -231,8 +231,12 @@ sdg_status plan_mesh(const sdg_mesh_desc* d, Plan& P) {
   P.o_tiles_bucket = take(sizeof(WgTile) * std::max(P.n_tiles[3], 1));
   P.o_stage_a = take(P.state_bytes);
   P.o_stage_b = take(P.state_bytes);
-  P.o_scratch = take(sizeof(double) * (size_t)(18 + 6 * P.F) * (size_t)P.n_slots);
-  P.o_tfac = take(sizeof(double) * 18 * (size_t)P.n_slots);   // the adjoint's transposed factors
+  // the column solves' scratch: the kept P_l, or for the serial sweeps E_l and y_l and,
+  // in double, the adjoint's transposed factors
+  const size_t cs = P.prec == SDG_FP32 ? sizeof(float) : sizeof(double);
+  const bool blocks = !P.col_tiles.empty();
+  P.o_scratch = take(cs * (size_t)(blocks ? 10 : 18 + 6 * P.F) * (size_t)P.n_slots);
+  P.o_tfac = take(blocks || P.fp32 ? 0 : sizeof(double) * 18 * (size_t)P.n_slots);
   P.o_colmass = take(sizeof(double) * (size_t)P.F * P.CS);
   P.o_msum = take(sizeof(double) * (size_t)P.F * P.n_members);
   P.o_flag = take(sizeof(int32_t) * 64);
@@ -814,10 +818,11 @@ hipError_t enqueue_column_solve(sdg_ctx* ctx, const void* Tstar, void* Tout, dou
   return launch_column_solve(a, ctx->plan.fp32, ctx->plan.prec == SDG_FP32, transposed, strm);
 }
 
-// The transposed system's factors for the adjoint's solve over dt, kept in
-// their own array (the forward factors stay valid).
+// The factors for the adjoint's solve over dt.  The layer-parallel solve uses the
+// forward system's; the serial sweep has its own, kept in their own array (the forward
+// factors stay valid).
 sdg_status ensure_tfactors(sdg_ctx* ctx, double dt, hipStream_t strm) {
-  if (!ctx->plan.col_tiles.empty()) return ensure_factors(ctx, dt, strm);   // both systems share the pivots
+  if (!ctx->plan.col_tiles.empty()) return ensure_factors(ctx, dt, strm);
   if (ctx->tfac_valid && ctx->tfac_dt == dt) return SDG_OK;
   hipError_t e = launch_tsolve(ctx->dm, ctx->plan.F, nullptr, nullptr, ctx->kappa, ctx->tfac, dt, ctx->eta, true, strm);
   if (e != hipSuccess) return hip_fail(e, "transposed column factor launch");

@@ -53,6 +53,19 @@ def test_layout_matches_cell_formula():
     assert L.workspace_bytes > 2 * L.state_bytes
 
 
+@pytest.mark.parametrize("precision", [P.SDG_FP64, P.SDG_FP32, P.SDG_FP32_STATE_FP64_SOLVE])
+@pytest.mark.parametrize("layers,fields", [(1, 2), (2, 2), (30, 4), (64, 1)])
+def test_workspace_holds_no_serial_factors_for_blocks(layers, fields, precision):
+    """Up to 64 layers the column solves keep 10 values a slot (80 bytes in double, 40
+    all float) besides the two stage buffers and the mesh."""
+    w = W.tiny(n=12, n_layers=layers, n_fields=fields)
+    L = P.Mesh.from_workload(w, precision).layout()
+    columns = 64 * L.n_cells
+    mesh = 36 * (L.n_slots + columns) + 1024 * columns       # level heights (double and float), per-column tables
+    solve = (40 if precision == P.SDG_FP32 else 80) * L.n_slots
+    assert L.workspace_bytes <= 2 * L.state_bytes + solve + mesh + (1 << 16)
+
+
 def test_fp32_layout_halves_state():
     w = W.tiny(n_fields=3)
     L64 = P.Mesh.from_workload(w, P.SDG_FP64).layout()
