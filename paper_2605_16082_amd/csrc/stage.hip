@@ -45,6 +45,7 @@
 #include <atomic>
 
 #include "internal.h"
+#include "quadrature.h"
 
 // Multiply-adds are fused only within one expression, never across
 // statements, so the shared device functions below round the same way in
@@ -53,25 +54,6 @@
 
 namespace sdg {
 namespace {
-
-// 6-point triangle rule: barycentric points (lambda0, lambda1, lambda2);
-// weights include the reference-triangle area 1/2.
-constexpr double kA1 = 0.44594849091596488631832925388305199;
-constexpr double kB1 = 0.10810301816807022736334149223390401;
-constexpr double kW1 = 0.5 * 0.22338158967801146569500700843312280;
-constexpr double kA2 = 0.091576213509770743459571463402201508;
-constexpr double kB2 = 0.81684757298045851308085707319559698;
-constexpr double kW2 = 0.5 * 0.10995174365532186763832632490021053;
-constexpr double kL0[6] = {kB1, kA1, kA1, kB2, kA2, kA2};
-constexpr double kL1[6] = {kA1, kA1, kB1, kA2, kA2, kB2};
-constexpr double kL2[6] = {kA1, kB1, kA1, kA2, kB2, kA2};
-constexpr double kTw[6] = {kW1, kW1, kW1, kW2, kW2, kW2};
-// zeta = -1/sqrt(3), +1/sqrt(3): t = (1+zeta)/2, b = (1-zeta)/2; weights 1.
-constexpr double kZt[2] = {0.21132486540518711774542560974902127, 0.78867513459481288225457439025097873};
-constexpr double kZb[2] = {0.78867513459481288225457439025097873, 0.21132486540518711774542560974902127};
-// 3-point Gauss on [0, 1].
-constexpr double kS[3] = {0.11270166537925831148207346002176005, 0.5, 0.88729833462074168851792653997823995};
-constexpr double kSw[3] = {5.0 / 18.0, 8.0 / 18.0, 5.0 / 18.0};
 
 template <typename R> __device__ __forceinline__ const R* geo_of(const DevMesh& m);
 template <> __device__ __forceinline__ const double* geo_of<double>(const DevMesh& m) { return m.geo; }
@@ -1154,7 +1136,6 @@ __global__ __launch_bounds__(64) void walk_kernel(StageArgs a) {
     wc.base = (uint32_t)m.cell_base[cell];
     wc.lbase = (uint32_t)m.cell_lbase[cell];
     wc.depth = (int)(((uint32_t)m.cell_base[cell + 1] - wc.base) / kCell);
-    const int depth = wc.depth;
     const int l0 = tile.layer0;
     const int l1 = l0 + tile.nlay;
     const size_t S = (size_t)m.n_slots;

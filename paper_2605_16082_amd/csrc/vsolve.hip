@@ -26,12 +26,13 @@
 // y_l = D'_l^-1 r'_l; back substitution x_l = y_l - E_l (C_l x_{l+1})
 // recomputes C_l from the levels.
 //
-// These serial sweeps serve meshes with a column deeper than 64 layers; the
-// others take the layer-parallel solve of column_solve.hip.
+// These serial sweeps serve whole meshes with a column deeper than 64 layers, and
+// all-float ones of two layers and three or four fields; the others take the
+// layer-parallel solve of column_solve.hip.
 //
 // E_l depends only on the mesh, kappa, dt and the penalty, not on the
 // fields, so it is computed once for a given (kappa, dt, eta) by a sweep
-// without fields (factor_kernel) and kept in scratch; each solve's forward
+// without fields (vsolve_kernel with NF = 0) and kept in scratch; each solve's forward
 // sweep recomputes it in registers (its LU is needed for y) but stores only
 // y_l, and the back substitution reads the kept E_l.  That moves 18 values
 // per prism slot fewer than storing E with every solve (FP64 solve 1.39 ->
@@ -43,20 +44,10 @@
 // is double (the FP64 and FP32-state/FP64-solve forms) or float (the
 // FP32-everywhere form); the scratch then holds values of type C.
 #include "internal.h"
+#include "quadrature.h"
 
 namespace sdg {
 namespace {
-
-constexpr double kA1 = 0.44594849091596488631832925388305199;
-constexpr double kB1 = 0.10810301816807022736334149223390401;
-constexpr double kW1 = 0.5 * 0.22338158967801146569500700843312280;
-constexpr double kA2 = 0.091576213509770743459571463402201508;
-constexpr double kB2 = 0.81684757298045851308085707319559698;
-constexpr double kW2 = 0.5 * 0.10995174365532186763832632490021053;
-constexpr double kL0[6] = {kB1, kA1, kA1, kB2, kA2, kA2};
-constexpr double kL1[6] = {kA1, kA1, kB1, kA2, kA2, kB2};
-constexpr double kL2[6] = {kA1, kB1, kA1, kA2, kB2, kA2};
-constexpr double kTw[6] = {kW1, kW1, kW1, kW2, kW2, kW2};
 
 // symmetric 3x3 storage: 0:00 1:11 2:22 3:01 4:02 5:12
 __device__ __forceinline__ int sidx(int a, int b) {
@@ -243,7 +234,6 @@ __global__ __launch_bounds__(64) void vsolve_kernel(SolveArgs a) {
 
     // Schur complement with the layer above
     if (l > 0) {
-      C P[3][3];
       // B_l = dt [-kp Kvp/2 | kp Kvp/2 - sig_u S]  (3 x 6)
       C Bm[3][6];
 #pragma unroll
@@ -264,6 +254,7 @@ __global__ __launch_bounds__(64) void vsolve_kernel(SolveArgs a) {
           Cm[i][j] = hk - dt * sig_u * (i == j ? sd : so);
           Cm[i][j + 3] = -hk;
         }
+      C P[3][3];
 #pragma unroll
       for (int i = 0; i < 3; ++i)
 #pragma unroll
