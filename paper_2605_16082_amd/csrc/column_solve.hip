@@ -11,7 +11,8 @@
 //   up:    v_l = C_{l-1} x_l     = d_l - H_l v_{l+1}
 //   x_l = D'_l^-1 (M T*_l - [u_{l-1}; 0] - [0; v_{l+1}])
 // A block holds a group of columns over all their layers; (K, c) and (H, d)
-// go through LDS, where one lane per (column, field) runs the two 3x3 chains.
+// go through LDS, where a quad of lanes per (column, field) runs the two 3x3 chains,
+// a lane per component.
 // The transposed system has the same pivots (its block LU factors are the
 // transposes): with q the forward intermediate, the chains carry q_l's bottom
 // and mu_l's top values with K = H_fwd^T and H = K_fwd^T, so both systems use
@@ -21,28 +22,18 @@
 // for deeper columns: that sweep moves 114 values per prism and field set of
 // four (y_l makes a round trip through memory, E_l is read) and repeats an LU
 // per layer in one serial chain; here a prism moves its right-hand side, its
-// solution, the 9 kept values and its heights (60 values), and the serial part is
-// 9 multiply-adds a layer.  One solve before -> now: 199,712 x 30 prisms, 4
+// solution, the 9 kept values and its heights (60 values), and the serial part is a
+// chain of three multiply-adds and a lane exchange a layer, twice.  One solve before -> now: 199,712 x 30 prisms, 4
 // fields, double 1158 -> 800 us (2.9 GB at 3.6 TB/s; some 70 us less without the
 // two chains, 90 without the stores: a block's loads all come at its start, so
 // memory idles while it computes), float state 1033 -> 606, float 586 -> 480;
 // 68,220 ragged columns to 60 layers, 4 fields 1106 -> 452; 49,928 x 20, 1 field
 // 115 -> 64; 1,800 x 10, 1 field 32 -> 7.
 #include "internal.h"
+#include "quadrature.h"
 
 namespace sdg {
 namespace {
-
-constexpr double kA1 = 0.44594849091596488631832925388305199;
-constexpr double kB1 = 0.10810301816807022736334149223390401;
-constexpr double kW1 = 0.5 * 0.22338158967801146569500700843312280;
-constexpr double kA2 = 0.091576213509770743459571463402201508;
-constexpr double kB2 = 0.81684757298045851308085707319559698;
-constexpr double kW2 = 0.5 * 0.10995174365532186763832632490021053;
-constexpr double kL0[6] = {kB1, kA1, kA1, kB2, kA2, kA2};
-constexpr double kL1[6] = {kA1, kA1, kB1, kA2, kA2, kB2};
-constexpr double kL2[6] = {kA1, kB1, kA1, kA2, kB2, kA2};
-constexpr double kTw[6] = {kW1, kW1, kW1, kW2, kW2, kW2};
 
 template <typename C>
 struct alignas(2 * sizeof(C)) CPair {
@@ -90,7 +81,7 @@ __device__ __forceinline__ M3<C> inv3(const M3<C>& a) {
   return r;
 }
 
-// base + sign * a b
+// a b, and base - a b
 template <typename C>
 __device__ __forceinline__ M3<C> mul3(const M3<C>& a, const M3<C>& b) {
   M3<C> r;
@@ -140,6 +131,36 @@ __device__ __forceinline__ void couple_v(const C Q[6], const C x[3], const C y[3
   const C s = z[0] + z[1] + z[2];
 #pragma unroll
   for (int i = 0; i < 3; ++i) out[i] = Q[sx(i, 0)] * e0 + Q[sx(i, 1)] * e1 + Q[sx(i, 2)] * e2 - t * (s + z[i]);
+}
+
+// Q = scale sum_q w lambda lambda / D(q), D the thickness at the triangle rule's points.
+template <typename C>
+__device__ __forceinline__ void coupling_q(C scale, const C dz[3], C Q[6]) {
+#pragma unroll
+  for (int i = 0; i < 6; ++i) Q[i] = (C)0;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    const C inv = (C)kTw[q] * recip((C)kL0[q] * dz[0] + (C)kL1[q] * dz[1] + (C)kL2[q] * dz[2]);
+    Q[0] += (C)(kL0[q] * kL0[q]) * inv;
+    Q[1] += (C)(kL1[q] * kL1[q]) * inv;
+    Q[2] += (C)(kL2[q] * kL2[q]) * inv;
+    Q[3] += (C)(kL0[q] * kL1[q]) * inv;
+    Q[4] += (C)(kL0[q] * kL2[q]) * inv;
+    Q[5] += (C)(kL1[q] * kL2[q]) * inv;
+  }
+#pragma unroll
+  for (int i = 0; i < 6; ++i) Q[i] *= scale;
+}
+// Mz / (3 J_h)
+template <typename C>
+__device__ __forceinline__ void mass_third(const C dz[3], C mz[6]) {
+  const C s = (C)(1.0 / 360.0);
+  mz[0] = s * ((C)3 * dz[0] + dz[1] + dz[2]);
+  mz[1] = s * (dz[0] + (C)3 * dz[1] + dz[2]);
+  mz[2] = s * (dz[0] + dz[1] + (C)3 * dz[2]);
+  mz[3] = s * (dz[0] + dz[1] + (C)0.5 * dz[2]);
+  mz[4] = s * (dz[0] + dz[2] + (C)0.5 * dz[1]);
+  mz[5] = s * (dz[1] + dz[2] + (C)0.5 * dz[0]);
 }
 
 // y -= D'^-T g with g = [Q s - t S s; -Q s] (above: the coupling C_{l-1}^T s) or
@@ -316,8 +337,8 @@ column_solve_kernel(ColSolveArgs a) {
   const int cs = tile.col + col;
   const int N = m.nlay[cs];
   const bool live = l < N;
-  C* __restrict__ chK = reinterpret_cast<C*>(smem);
-  C* __restrict__ chC = chK + 9 * kRow;
+  C* chK = reinterpret_cast<C*>(smem);   // over the staged right-hand sides, once they are read
+  C* chC = chK + 9 * kRow;
   const uint32_t p = (uint32_t)tile.base + (uint32_t)l * kCell + (uint32_t)col;
   const uint32_t po = p * (uint32_t)sizeof(S);
 
@@ -358,34 +379,9 @@ column_solve_kernel(ColSolveArgs a) {
     const C pen = dt * eta * (C)(0.5 / 24.0);
     if (up) tu = pen * ((C)a.kappa[l - 1] + kc) * recip(hu < h ? hu : h);
     if (dn) td = pen * (kc + (C)a.kappa[l + 1]) * recip(h < hd ? h : hd);
-    // Q = dt kappa/2 sum_q w lambda lambda / D(q)
-    {
-      const C s = (C)0.5 * dt * kc;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) Q[i] = (C)0;
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        const C inv = (C)kTw[q] * recip((C)kL0[q] * dz[0] + (C)kL1[q] * dz[1] + (C)kL2[q] * dz[2]);
-        Q[0] += (C)(kL0[q] * kL0[q]) * inv;
-        Q[1] += (C)(kL1[q] * kL1[q]) * inv;
-        Q[2] += (C)(kL2[q] * kL2[q]) * inv;
-        Q[3] += (C)(kL0[q] * kL1[q]) * inv;
-        Q[4] += (C)(kL0[q] * kL2[q]) * inv;
-        Q[5] += (C)(kL1[q] * kL2[q]) * inv;
-      }
-#pragma unroll
-      for (int i = 0; i < 6; ++i) Q[i] *= s;
-    }
+    coupling_q((C)0.5 * dt * kc, dz, Q);
     weak = kCorrect && tu + td + (C)8 * Q[0] < (C)0.2 * h;
-    {
-      const C s = (C)(1.0 / 360.0);
-      mz[0] = s * ((C)3 * dz[0] + dz[1] + dz[2]);
-      mz[1] = s * (dz[0] + (C)3 * dz[1] + dz[2]);
-      mz[2] = s * (dz[0] + dz[1] + (C)3 * dz[2]);
-      mz[3] = s * (dz[0] + dz[1] + (C)0.5 * dz[2]);
-      mz[4] = s * (dz[0] + dz[2] + (C)0.5 * dz[1]);
-      mz[5] = s * (dz[1] + dz[2] + (C)0.5 * dz[0]);
-    }
+    mass_third(dz, mz);
     {
       // D'_l = [tt tb; bt bb]
       M3<C> tt, tb, bt, bb;
@@ -649,33 +645,9 @@ __global__ __launch_bounds__(64) void column_factor_kernel(ColFactorArgs a) {
     const C kn2 = kap(l + 2);
     mean(g1);
     const C td = pen * (kc + kn) * recip(g0.h < g1.h ? g0.h : g1.h);
-    // Q = dt kappa/2 sum_q w lambda lambda / D(q)
     C Q[6], mz[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) Q[i] = (C)0;
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      const C inv = (C)kTw[q] * recip((C)kL0[q] * g0.dz[0] + (C)kL1[q] * g0.dz[1] + (C)kL2[q] * g0.dz[2]);
-      Q[0] += (C)(kL0[q] * kL0[q]) * inv;
-      Q[1] += (C)(kL1[q] * kL1[q]) * inv;
-      Q[2] += (C)(kL2[q] * kL2[q]) * inv;
-      Q[3] += (C)(kL0[q] * kL1[q]) * inv;
-      Q[4] += (C)(kL0[q] * kL2[q]) * inv;
-      Q[5] += (C)(kL1[q] * kL2[q]) * inv;
-    }
-    const C sq = (C)0.5 * dt * kc;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) Q[i] *= sq;
-    {
-      const C s = (C)(1.0 / 360.0);
-      const C* dz = g0.dz;
-      mz[0] = s * ((C)3 * dz[0] + dz[1] + dz[2]);
-      mz[1] = s * (dz[0] + (C)3 * dz[1] + dz[2]);
-      mz[2] = s * (dz[0] + dz[1] + (C)3 * dz[2]);
-      mz[3] = s * (dz[0] + dz[1] + (C)0.5 * dz[2]);
-      mz[4] = s * (dz[0] + dz[2] + (C)0.5 * dz[1]);
-      mz[5] = s * (dz[1] + dz[2] + (C)0.5 * dz[0]);
-    }
+    coupling_q((C)0.5 * dt * kc, g0.dz, Q);
+    mass_third(g0.dz, mz);
     // D'_l = [tt tb; bt bb] (a layer below exists); its inverse's right blocks
     const C fu = l > 0 ? (C)1 : (C)2;
     M3<C> tt, tb, bt, bb;
