@@ -1038,11 +1038,17 @@ hipError_t launch_adj_stage_nf(const AdjStageArgs& a, bool w_zero, int tile_laye
   // no wavefronts for layers that no cell has, as in the forward stages
   const int layers = tile_layers < a.m.max_layers ? tile_layers : a.m.max_layers;
   const dim3 grid(a.n_tiles), block(kCell * layers);
-  // more than 16 wavefronts per CU: neighbours in the cell through LDS.  Reverse step
-  // (three of these kernels and a solve), without -> with LDS, FP64: 15602 wavefronts 1
-  // field 317 -> 288 us, 2 fields 492 -> 437, 4 fields 851 -> 808; 4050 wavefronts 88.6
-  // -> 87.4, 121 -> 120, 195 -> 200; 897 wavefronts 37.5 -> 39.7, 48.8 -> 50.2, 66 -> 67.
-  if ((int64_t)a.n_tiles * layers > 16 * (int64_t)n_cu) {
+  // more than 16 wavefronts per CU, with four fields 28: neighbours in the cell through
+  // LDS.  Reverse step (three of these kernels and a solve), 1 to 4 fields, without ->
+  // with LDS:
+  //    1469 wavefronts   46.5  59.1  80.8  93.5 ->  44.3  57.7  74.3  95.6 us
+  //    3000              75.2  97.0   136   160 ->  73.7  98.2   131   170
+  //    4140              91.1   121   165   200 ->  87.8   119   161   213
+  //    6210               125   167   239   312 ->   120   164   240   319
+  //    8100               151   204   342   429 ->   143   205   302   420
+  //   15602               317   492     -   851 ->   288   437     -   808
+  constexpr int kLine = NF == 4 ? 28 : 16;
+  if ((int64_t)a.n_tiles * layers > kLine * (int64_t)n_cu) {
     const size_t lds = block.x * kAdjRows<NF> * sizeof(double);
     if (w_zero) hipLaunchKernelGGL((adj_stage_kernel<NF, true, true>), grid, block, lds, s, a);
     else hipLaunchKernelGGL((adj_stage_kernel<NF, false, true>), grid, block, lds, s, a);

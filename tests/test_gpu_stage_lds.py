@@ -72,3 +72,32 @@ def test_adjoint_step_is_the_transpose(fields, w_zero):
         right = float(s.m_dot(d, z).sum())
         scale = (float(s.m_dot(ad, ad).sum()) * float(s.m_dot(y, y).sum())) ** 0.5
         assert abs(left - right) <= 1e-12 * scale, shape
+
+
+@pytest.mark.parametrize("w_zero", [True, False])
+def test_adjoint_step_of_four_fields_is_the_transpose(w_zero):
+    """The same above the line of four fields (28 wavefronts per CU), and the shapes agree
+    bitwise."""
+    w, s, state = _build(116, 28, 4, P.SDG_FP64, w_zero)
+    rng = np.random.default_rng(11)
+    d = s.scatter(rng.standard_normal(w.T0.shape))
+    y = s.scatter(rng.standard_normal(w.T0.shape))
+    ends = []
+    for x0 in (d, s.new_state()):
+        x = x0.clone()
+        s.set_fields(x)
+        s.step()
+        ends.append(x)
+    ad = ends[0] - ends[1]
+    ref = None
+    for shape in [(2, 1, 0), (1, 1, 0), (4, 0, 0)]:
+        s.set_tuning(*shape)
+        z = s.new_state()
+        s.step_adjoint(y, z)
+        s.sync()
+        left = float(s.m_dot(ad, y).sum())
+        right = float(s.m_dot(d, z).sum())
+        scale = (float(s.m_dot(ad, ad).sum()) * float(s.m_dot(y, y).sum())) ** 0.5
+        assert abs(left - right) <= 1e-12 * scale, shape
+        ref = s.gather(z) if ref is None else ref
+        assert np.array_equal(s.gather(z), ref), shape
