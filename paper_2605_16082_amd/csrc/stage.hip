@@ -669,8 +669,8 @@ __device__ __forceinline__ TileRange tile_range(const StageArgs& a) {
 // A launch of at most one wavefront per SIMD has only its own chain of latencies, to
 // which LDS adds: launch_mode draws the line there.  Third stage in blocks of two
 // layers, without -> with LDS (without: one wavefront per SIMD, see stage_kernel):
-//   904 wavefronts   FP64 1-4 fields  7.5 9.6 12.1 13.6 -> 9.9 12.7 15.7 17.8 us
-//                    FP32             5.4 6.8  8.0  9.2 -> 5.9  7.5  8.7 10.2
+//   904 wavefronts   FP64 1-4 fields  7.5 9.6 12.2 13.4 -> 9.9 12.7 15.7 17.8 us
+//                    FP32             5.6 7.1  8.4 10.2 -> 5.9  7.5  8.7 10.2
 // and on the line's other side, where more than one wavefront has to fit a SIMD:
 //   1130 wavefronts  FP64            10.3 12.9 18.5 21.0 -> 10.9 13.8 17.0 19.6
 //                    FP32             6.9  8.6 10.5 12.6 ->  6.2  7.8  9.4 11.4
@@ -829,13 +829,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const WgTile tile
   }
 }
 
-// Without SH the launch has at most one wavefront per SIMD, and the kernel reserves
-// more than half of a SIMD's registers so that it gets them so: of two blocks of two
-// wavefronts the dispatcher puts the second on the SIMDs of the first while others
-// idle, where both fit.  Third stage of 640 wavefronts in blocks of two, both fitting ->
-// reserved: FP64 1 field 9.0 -> 7.3 us, 2 fields 11.5 -> 9.2, FP32 4 fields 10.0 -> 9.1.
+// Without SH the launch has at most one wavefront per SIMD.  In double with one or two
+// fields the kernel then reserves more than half of a SIMD's registers, as with three
+// and four fields it needs: of two blocks of two wavefronts the dispatcher puts the
+// second on the SIMDs of the first while others idle, where both fit.  Third stage of
+// 640 wavefronts in blocks of two, both fitting -> reserved: 1 field 9.0 -> 7.3 us, 2
+// fields 11.5 -> 9.2.  In float it gains less (4 fields 10.0 -> 9.1), and steps of four
+// streams side by side lose (904 wavefronts each, 20 -> 22 us a step).
 template <typename R, int NF, bool WZ, bool RHS, bool READ_TN, bool OUT2, bool SH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, SH ? 8 : 1))) void stage_kernel(StageArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, !SH && sizeof(R) == 8 && NF <= 2 ? 1 : 8)))
+void stage_kernel(StageArgs a) {
   // each wavefront's own rows: the LDS accesses of a wavefront complete in order, so
   // they need no barrier, neither within a tile nor from one tile to the next
   extern __shared__ __align__(16) char stage_lds[];

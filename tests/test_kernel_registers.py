@@ -1,6 +1,7 @@
 """Registers that the built kernels reserve, read from their kernel descriptors: the
-stage kernel of launches of at most one wavefront per SIMD takes more than half of a
-SIMD's 512, so that no two of its wavefronts share one."""
+double stage kernel of launches of at most one wavefront per SIMD, and the solve kernel of
+two-layer ones, take more than half of a SIMD's 512, so that no two of their wavefronts
+share one."""
 
 import os
 import re
@@ -34,8 +35,9 @@ def _reserved(tmp_path, kernel):
 
 def test_small_stage_launches_get_a_simd_for_each_wavefront(tmp_path):
     regs = _reserved(tmp_path, "12stage_kernel")
-    small = {k: v for k, v in regs.items() if k.endswith("Lb0EEEvNS_9StageArgsE")}   # the last argument: SH
-    assert len(small) == 64 and len(regs) == 128
+    # <double, fields, ..., no LDS>
+    small = {k: v for k, v in regs.items() if "kernelId" in k and k.endswith("Lb0EEEvNS_9StageArgsE")}
+    assert len(small) == 32 and len(regs) == 128
     assert min(small.values()) > 256, min(small.items(), key=lambda kv: kv[1])
 
 
