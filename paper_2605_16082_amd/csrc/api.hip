@@ -51,7 +51,7 @@ struct Plan {
   // (the horizontal diffusion stages their values in LDS): offsets, largest count
   std::vector<int32_t> halo_off;
   int halo_max = 0;
-  // cells deepest first (stable): the dispatch order of the column solves
+  // cells deepest first (stable): the order of the column sweeps and of the solves' blocks
   std::vector<int32_t> cell_order;
   int n_tiles[kTileChoices] = {};
   // blocks of the layer-parallel column solves (empty: the serial sweeps are used)

@@ -23,12 +23,12 @@
 // four (y_l makes a round trip through memory, E_l is read) and repeats an LU
 // per layer in one serial chain; here a prism moves its right-hand side, its
 // solution, the 9 kept values and its heights (60 values), and the serial part is a
-// chain of three multiply-adds and a lane exchange a layer, twice.  One solve before -> now: 199,712 x 30 prisms, 4
-// fields, double 1158 -> 800 us (2.9 GB at 3.6 TB/s; some 70 us less without the
-// two chains, 90 without the stores: a block's loads all come at its start, so
-// memory idles while it computes), float state 1033 -> 606, float 586 -> 480;
-// 68,220 ragged columns to 60 layers, 4 fields 1106 -> 452; 49,928 x 20, 1 field
-// 115 -> 64; 1,800 x 10, 1 field 32 -> 7.
+// chain of three multiply-adds and a lane exchange a layer, twice.  One solve before ->
+// now: 199,712 x 30 prisms, 4 fields, double 1158 -> 800 us (2.9 GB at 3.6 TB/s; 714 to
+// 764 on other cards; some 70 us less without the two chains, 90 without the stores: a
+// block's loads all come at its start, so memory idles while it computes), float state
+// 1033 -> 606, float 586 -> 480; 68,220 ragged columns to 60 layers, 4 fields 1106 -> 452;
+// 49,928 x 20, 1 field 115 -> 64; 1,800 x 10, 1 field 32 -> 7.
 #include "internal.h"
 #include "quadrature.h"
 

@@ -60,8 +60,8 @@ struct DevMesh {
   const int32_t* halo_slot;
   const int32_t* halo_depth;
   const int32_t* halo_idx;     // [3][n_col_slots]
-  // the cells deepest first: the column solves take their cells in this
-  // order, so the longest columns do not end the launch alone
+  // the cells deepest first: the factor sweep and the serial column sweeps take
+  // their cells in this order, so the longest columns do not end the launch alone
   const int32_t* cell_order;   // [n_cells]
 };
 
